@@ -90,6 +90,7 @@ struct Item {
   uint32_t count;
   bool tall;
   bool direct;         // bf16: iteration 1 reads the caller's matrix in place of a padded copy
+  bool pair;           // bf16: two iterations per update (see pair_rule)
 };
 
 // Which items a launch covers (the others get no blocks).
@@ -280,6 +281,7 @@ tm_status fire(const Plan& pl, int kind, int cfg, const Phase& P) {
       return fail(TM_ERR_HIP, "hipEventCreate failed");
     (void)hipEventRecord(tl.start, pl.st);
   }
+  if (P.total <= 0) return TM_OK;
   hipError_t e;
   if (pl.esz == 4)
     e = tmk::launch_phase_f32(kind, cfg, P, pl.st);
@@ -302,11 +304,38 @@ struct Run {
   size_t first, n;
 };
 
+// Per-class operands of a bf16 matrix-core step (see Phase).
+struct Step {
+  int kind;
+  uint32_t flags;
+  int src = 0, dst = 0;       // Gram, update: Y slots
+  int fac = tmk::kBufB;       // update: its k x k factor
+  // k x k product: out = alpha L R + beta M + gamma I
+  int l = 0, r = 0, m = tmk::kNoBuf, out = 0, mode = tmk::kSymBf16;
+  float alpha = 0.f, beta = 0.f, gamma = 0.f;
+};
+
+// Tile of one bf16 matrix-core launch over `items` (those it covers).  A call
+// that runs its update over all of its matrices in one launch keeps the
+// layout tile.
+int choose_step_cfg(int kind, uint32_t flags, int tcfg, const std::vector<Item>& items, bool whole) {
+  if (kind == tmk::kKindUpdate) return whole ? tcfg : choose_update_cfg(tcfg, items);
+  // the first Gram's row partials and fp32 tiles want at least 64 columns
+  const bool small = kind == tmk::kKindPoly || (flags & (tmk::kRowSum | tmk::kA32)) == 0u;
+  return choose_sym_cfg(kind, tcfg, items, small);
+}
+
 // One launch of `kind` per chunk of at most kMaxEntries entries and kMaxPtrs
-// table pointers.
+// table pointers.  bf16 matrix-core steps pass their operands by class in
+// `steps` (a null one leaves its class out).
 tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, float b, float c,
-                 uint32_t flags, int aux, Cover cover = kCoverAll) {
+                 uint32_t flags, int aux, Cover cover = kCoverAll,
+                 const Step* const* steps = nullptr) {
   const std::vector<Item>& items = *pl.items;
+  auto covered = [&](const Item& it) {
+    return !((cover == kCoverTall && !it.tall) || (cover == kCoverCopied && it.direct) ||
+             (steps != nullptr && steps[it.pair ? 1 : 0] == nullptr));
+  };
   // update launches take their largest products first (the longest tiles
   // start first); every entry carries its own workspace offset
   std::vector<size_t> idx(items.size());
@@ -321,7 +350,7 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     const Item& u = items[idx[prev]];
     const Item& v = items[idx[next]];
     return u.count == 1u && v.count == 1u && u.k == v.k && u.N == v.N && u.kp == v.kp &&
-           u.Np == v.Np && u.tall == v.tall && u.direct == v.direct &&
+           u.Np == v.Np && u.tall == v.tall && u.direct == v.direct && u.pair == v.pair &&
            pl.ws_off[idx[next]] == pl.ws_off[idx[prev]] + item_ws(u, pl.esz);
   };
   std::vector<std::vector<Run>> chunks(1);
@@ -346,18 +375,17 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
   for (const std::vector<Run>& ch : chunks) {
     Phase P;
     std::memset(&P, 0, sizeof(P));
-    // a call split over several launches picks each launch's tile for that
-    // launch's matrices (the last one may be much smaller); a product's
-    // arithmetic does not depend on the tile size
+    // each launch picks its tile for the matrices that it covers (the last
+    // launch of a split call may have much fewer); a product's arithmetic does
+    // not depend on the tile size
     int ccfg = cfg;
-    if (pl.esz == 2 && chunks.size() > 1 &&
-        (kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate)) {
-      std::vector<Item> chunk;
+    if (steps != nullptr) {
+      std::vector<Item> part;
       for (const Run& r : ch)
-        for (size_t i = r.first; i < r.first + r.n; ++i) chunk.push_back(items[idx[i]]);
-      ccfg = kind == tmk::kKindUpdate
-                 ? choose_update_cfg(pl.tcfg, chunk)
-                 : choose_sym_cfg(kind, pl.tcfg, chunk, kind == tmk::kKindPoly || flags == 0u);
+        for (size_t i = r.first; i < r.first + r.n; ++i)
+          if (covered(items[idx[i]])) part.push_back(items[idx[i]]);
+      if (part.empty()) continue;
+      ccfg = choose_step_cfg(kind, flags, pl.tcfg, part, part.size() == items.size());
     }
     uint64_t start = 0;
     uint32_t xp = 0;
@@ -373,15 +401,19 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
       E.kp = it.kp;
       E.Np = it.Np;
       E.count = r.n > 1 ? uint32_t(r.n) : it.count;
-      E.flags = (it.tall ? tmk::kTall : 0u) | (it.direct ? tmk::kDirect : 0u);
+      E.flags = (it.tall ? tmk::kTall : 0u) | (it.direct ? tmk::kDirect : 0u) |
+                (it.pair ? tmk::kPair : 0u);
+      if (steps != nullptr && steps[it.pair ? 1 : 0] != nullptr) {
+        const Step& st = *steps[it.pair ? 1 : 0];
+        E.flags |= tmk::pack_ops(st.src, st.dst, st.fac, st.l, st.r, st.m, st.out);
+      }
       if (r.n > 1) {
         E.flags |= tmk::kPtrTab;
         E.xbase = xp;
         for (size_t i = r.first; i < r.first + r.n; ++i) P.xp[xp++] = items[idx[i]].x;
       }
       E.tile_start = uint32_t(start);
-      const bool skip = (cover == kCoverTall && !it.tall) || (cover == kCoverCopied && it.direct);
-      E.tiles_per = skip ? 0u : tmk::blocks_per_matrix(kind, ccfg, it.k, it.N, it.kp, it.Np);
+      E.tiles_per = !covered(it) ? 0u : tmk::blocks_per_matrix(kind, ccfg, it.k, it.N, it.kp, it.Np);
       start += uint64_t(E.tiles_per) * E.count;
     }
     if (start >= (uint64_t(1) << 31))
@@ -394,6 +426,14 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     P.a = a;
     P.b = b;
     P.c = c;
+    if (steps != nullptr) {
+      const Step none{kind, 0u};
+      const Step& s0 = steps[0] ? *steps[0] : none;
+      const Step& s1 = steps[1] ? *steps[1] : none;
+      P.a = s0.gamma, P.b = s0.beta, P.c = s0.alpha;
+      P.a2 = s1.gamma, P.b2 = s1.beta, P.c2 = s1.alpha;
+      P.symmode = !steps[0] ? s1.mode : (!steps[1] ? s0.mode : int(tmk::kSymMixed));
+    }
     P.flags = flags;
     P.aux = aux;
     P.tail_base = 0;
@@ -572,15 +612,146 @@ uint32_t first_gram_flags(int precond) {
   return 0u;
 }
 
+// Scale vector s of a call that has formed its first Gram (gram_scale; for
+// Algorithm 1 the trace of the first Gram, ||X0||_F^2).
+tm_status first_scale(const Plan& pl, int precond, int part) {
+  if (precond == TM_PRECOND_FROBENIUS)
+    return launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob | tmk::kTrace, 0);
+  return gram_scale(pl, precond, part);
+}
+
+// Coefficients of iteration `it` (0-based).
+struct Triple {
+  float a, b, c;
+};
+Triple triple(const float* coeffs, int it) {
+  return coeffs ? Triple{coeffs[3 * it], coeffs[3 * it + 1], coeffs[3 * it + 2]} : Triple{kA, kB, kC};
+}
+
+// Whether a bf16 call may take iterations two at a time (pair_rule), with the
+// k x k matrices in fp16.  After any scaling sigma_max(X1) <= 1, so every A, T = B~ A and B~
+// of the call is bounded by its coefficients: with x the largest sigma^2,
+// |B~| <= max |q| over [0, x], q(x) = a + b x + c x^2, and the next x is the
+// largest x q(x)^2.  The call qualifies while A and T stay below 8 (32768 as
+// stored, half of fp16's largest) and B~ below 32 (32768).
+bool half_ok(int iters, const float* coeffs, int precond) {
+  if (precond == TM_PRECOND_NONE) return false;
+  double x = 1.02;   // the scale's own rounding
+  for (int it = 0; it < iters; ++it) {
+    const Triple t = triple(coeffs, it);
+    const double a = t.a, b = t.b, c = t.c;
+    auto q = [&](double v) { return a + b * v + c * v * v; };
+    double top = std::max(std::fabs(a), std::fabs(q(x)));
+    if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < x) top = std::max(top, std::fabs(q(-b / (2 * c))));
+    if (!(x <= 8.0 && top <= 32.0 && x * top <= 8.0)) return false;
+    double nx = 0.0;
+    constexpr int S = 128;
+    for (int i = 1; i <= S; ++i) {
+      const double v = x * i / S;
+      nx = std::max(nx, v * q(v) * q(v));
+    }
+    x = 1.02 * nx;   // between the samples, and the rounding of the products
+  }
+  return x <= 8.0;
+}
+
+// Two iterations per update (class 1).  Iterations k, k + 1 as printed take two
+// Grams, two polynomials and two updates, (6 N + 2 k) k^2 operations.  As
+// B~ and A are polynomials of one matrix, the second Gram is B~ A B~ and the
+// two updates are one by Q = B~' B~: one Gram, five k x k products (A A,
+// T = B~ A, B~ T, A' A', Q, upper halves) and one update, (3 N + 5 k) k^2.
+// The k x k matrices are fp16 (11 bits against bf16's 8), and one bf16
+// rounding of Y drops out: the error against 64 bits is about half of the
+// step-by-step form's on every spectrum tried.  More than two would be
+// fewer operations still, but the Gram's rounding error then grows by a^2 for
+// every further iteration and passes the step-by-step form's on spectra with
+// many small singular values.
+// The line: measured, 8 x 4096 x 14336 20.0 -> 14.6 ms, the 64 conv matrices (N = 9 k)
+// 534 -> 427 us, one 768 x 3072 matrix 125 -> 122 us; square matrices do as many
+// operations either way and lose (8 x 4096 x 4096 7.4 -> 8.0 ms), N = 1.25 k saves 8%
+// of the operations.  Up to k = 32, one tile's k x k products are all latency.  The
+// matrices of the fused small-matrix kernel keep its step-by-step form.  The rule
+// depends on the shape alone, so that a matrix comes out the same from a single, a
+// batched and a grouped call.
+bool pair_rule(const Item& it) {
+  return it.k > 32 && 4 * uint64_t(it.N) >= 5 * uint64_t(it.k) && !small_eligible(it);
+}
+
+// The k x k products and update of iterations [it, it + n) of one class (1:
+// `pair`), n = 1 or 2, from A in kBufA; `scaled`: the update's factor times
+// diag(s).
+void block_steps(std::vector<Step>& out, bool pair, int it, int n, const float* coeffs, bool scaled,
+                 int src, int dst) {
+  const float sa = pair ? tmk::kScaleA : 1.f, sb = pair ? tmk::kScaleB : 1.f;
+  auto product = [&](int l, int r, int m, int o, float al, float be, float ga, bool factor) {
+    Step s{tmk::kKindPoly, 0u};
+    s.l = l, s.r = r, s.m = m, s.out = o;
+    s.alpha = al, s.beta = be, s.gamma = ga;
+    s.mode = !pair ? (scaled ? tmk::kSymBf16Scaled : tmk::kSymBf16)
+                   : (!factor ? tmk::kSymHalf : (scaled ? tmk::kSymFactorScaled : tmk::kSymFactor));
+    out.push_back(s);
+  };
+  // B~ = b A + c A A + a I, times `f` (1 for an update's factor, else kScaleB)
+  auto poly = [&](int i, int o, bool factor) {
+    const Triple t = triple(coeffs, i);
+    const float f = factor ? 1.f : sb;
+    product(tmk::kBufA, tmk::kBufA, tmk::kBufA, o, t.c * (f / (sa * sa)), t.b * (f / sa), t.a * f, factor);
+  };
+  Step u{tmk::kKindUpdate, 0u};
+  u.src = src;
+  u.dst = dst;
+  if (n == 1) {
+    poly(it, tmk::kBufB, true);
+  } else {
+    poly(it, tmk::kBufB, false);
+    product(tmk::kBufB, tmk::kBufA, tmk::kNoBuf, tmk::kBufT, 1.f / sb, 0.f, 0.f, false);   // T = B~ A
+    product(tmk::kBufB, tmk::kBufT, tmk::kNoBuf, tmk::kBufA, 1.f / sb, 0.f, 0.f, false);   // A' = B~ T
+    poly(it + 1, tmk::kBufT, false);                                                       // B~'
+    product(tmk::kBufT, tmk::kBufB, tmk::kNoBuf, tmk::kBufA, 1.f / (sb * sb), 0.f, 0.f, true);   // Q
+    u.fac = tmk::kBufA;
+  }
+  out.push_back(u);
+}
+
+// Runs the two classes' step lists, sharing launches where their kinds meet
+// in order (a longest common subsequence): classes that run apart would each
+// leave a partly filled last wave per launch.
+tm_status run_steps(const Plan& pl, const std::vector<Step> (&seq)[2]) {
+  const size_t n = seq[0].size(), m = seq[1].size();
+  auto meet = [&](size_t i, size_t j) {
+    const Step &a = seq[0][i], &b = seq[1][j];
+    return a.kind == b.kind && a.flags == b.flags &&
+           (a.kind != tmk::kKindPoly || (a.mode == tmk::kSymBf16 && b.mode == tmk::kSymHalf));
+  };
+  std::vector<int> best((n + 1) * (m + 1), 0);   // shared launches of the suffixes
+  auto at = [&](size_t i, size_t j) -> int& { return best[i * (m + 1) + j]; };
+  for (size_t i = n; i-- > 0;)
+    for (size_t j = m; j-- > 0;)
+      at(i, j) = meet(i, j) ? at(i + 1, j + 1) + 1 : std::max(at(i + 1, j), at(i, j + 1));
+  size_t i = 0, j = 0;
+  tm_status s = TM_OK;
+  while (s == TM_OK && (i < n || j < m)) {
+    const Step* st[2] = {nullptr, nullptr};
+    if (i < n && j < m && meet(i, j)) {
+      st[0] = &seq[0][i++];
+      st[1] = &seq[1][j++];
+    } else if (j == m || (i < n && at(i + 1, j) >= at(i, j + 1))) {
+      st[0] = &seq[0][i++];
+    } else {
+      st[1] = &seq[1][j++];
+    }
+    const Step& any = st[0] ? *st[0] : *st[1];
+    s = launch(pl, any.kind, 0, 0, 0, 0.f, 0.f, 0.f, any.flags, 0, kCoverAll, st);
+  }
+  return s;
+}
+
 // bf16: zero-padded tiled workspace, matrix-core kernels of tm_fast.hip.
-tm_status plan_bf16(const Plan& pl, int iters, const float* coeffs, int precond, int tcfg) {
+tm_status plan_bf16(const Plan& pl, int iters, const float* coeffs, int precond) {
   const bool frob = precond == TM_PRECOND_FROBENIUS;
   const bool from_gram = precond == TM_PRECOND_AOL || precond == TM_PRECOND_SCHATTEN4;
   const bool scaled = from_gram || frob;
   const uint32_t rflags = first_gram_flags(precond);
-  const int gcfg1 = choose_sym_cfg(tmk::kKindGram, tcfg, *pl.items);   // with row partials
-  const int gcfg = choose_sym_cfg(tmk::kKindGram, tcfg, *pl.items, true);
-  const int pcfg = choose_sym_cfg(tmk::kKindPoly, tcfg, *pl.items, true);
   const int part = tmk::kMinTile;   // the matrix-core Gram emits row partials per 64 columns
   // AOL with at most 16 row partials per row: the rescale pass sums s itself
   // (same order as the AOL-vector kernel), one launch fewer per call
@@ -590,39 +761,53 @@ tm_status plan_bf16(const Plan& pl, int iters, const float* coeffs, int precond,
   tm_status s = TM_OK;
   if (iters > 0 || from_gram)
     s = launch(pl, tmk::kKindLoadIn, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0, kCoverCopied);
-  if (s == TM_OK && frob) {  // Algorithm 1, first line: s = 1 / ||X0||_F
-    s = launch(pl, tmk::kKindFrob, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
-    if (s == TM_OK) s = launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob, 0);
-  }
   if (s != TM_OK) return s;
+  // the first Gram, of every matrix: A0 in fp32 where it is rescaled, then A1
+  Step g0{tmk::kKindGram, rflags | (scaled ? tmk::kA32 : 0u)};
+  g0.src = tmk::kSlotFirst;
+  const Step* const both[2] = {&g0, &g0};
+  auto gram = [&]() {
+    return launch(pl, g0.kind, 0, 0, 0, 0.f, 0.f, 0.f, g0.flags, 0, kCoverAll, both);
+  };
   if (iters == 0) {
-    if (from_gram) {
-      s = launch(pl, tmk::kKindGram, gcfg1, tmk::kSlotFirst, 0, 0.f, 0.f, 0.f, rflags | tmk::kA32, 0);
+    if (frob) {  // Algorithm 1, first line: s = 1 / ||X0||_F
+      s = launch(pl, tmk::kKindFrob, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
+      if (s == TM_OK) s = launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob, 0);
+    } else if (from_gram) {
+      s = gram();
       if (s == TM_OK) s = gram_scale(pl, precond, part);
-      if (s != TM_OK) return s;
     }
-    if (scaled) s = launch(pl, tmk::kKindApplyScale, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
+    if (s == TM_OK && scaled) s = launch(pl, tmk::kKindApplyScale, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
     return s;
   }
-  int src = tmk::kSlotFirst;
-  for (int it = 1; it <= iters && s == TM_OK; ++it) {
-    const float a = coeffs ? coeffs[3 * (it - 1)] : kA;
-    const float b = coeffs ? coeffs[3 * (it - 1) + 1] : kB;
-    const float c = coeffs ? coeffs[3 * (it - 1) + 2] : kC;
-    const int dst = it == iters ? tmk::kSlotFinal : (it % 2 == 1 ? tmk::kSlotAlt1 : tmk::kSlotAlt2);
-    const bool first = it == 1;
-    const uint32_t scale = (first && scaled) ? tmk::kScale : 0u;
-    const uint32_t gflags = (first ? rflags : 0u) | (scale ? tmk::kA32 : 0u);
-    s = launch(pl, tmk::kKindGram, gflags != 0u ? gcfg1 : gcfg, src, 0, 0.f, 0.f, 0.f, gflags, 0);
-    if (s == TM_OK && first && from_gram && !fuse_s) s = gram_scale(pl, precond, part);
-    if (s == TM_OK && scale)         // A1 = diag(s) A0 diag(s), one rounding
-      s = launch(pl, tmk::kKindScaleA, 0, 0, 0, 0.f, 0.f, 0.f, fuse_s ? tmk::kFuseS : 0u, part);
-    // with `scale` the polynomial stores B~ diag(s) and the update reads X0
-    if (s == TM_OK) s = launch(pl, tmk::kKindPoly, pcfg, 0, 0, a, b, c, scale, 0);
-    if (s == TM_OK) s = launch(pl, tmk::kKindUpdate, tcfg, src, dst, a, b, c, 0u, 0);
-    src = dst;
+  s = gram();
+  if (s == TM_OK && scaled && !fuse_s) s = first_scale(pl, precond, part);
+  if (s == TM_OK && scaled)         // A1 = diag(s) A0 diag(s), one rounding
+    s = launch(pl, tmk::kKindScaleA, 0, 0, 0, 0.f, 0.f, 0.f, fuse_s ? tmk::kFuseS : 0u, part);
+  if (s != TM_OK) return s;
+  // The iterations, from A1.  The first block's factor is stored times diag(s)
+  // and its update reads X0.
+  std::vector<Step> seq[2];
+  for (int cls = 0; cls < 2; ++cls) {
+    if (std::none_of(pl.items->begin(), pl.items->end(),
+                     [&](const Item& it) { return it.pair == (cls == 1); }))
+      continue;
+    int src = tmk::kSlotFirst;
+    for (int it = 0; it < iters;) {
+      const int n = cls == 1 ? std::min(2, iters - it) : 1;
+      const int dst = it + n == iters ? tmk::kSlotFinal
+                                      : (src == tmk::kSlotAlt1 ? tmk::kSlotAlt2 : tmk::kSlotAlt1);
+      if (it > 0) {
+        Step g{tmk::kKindGram, 0u};
+        g.src = src;
+        seq[cls].push_back(g);
+      }
+      block_steps(seq[cls], cls == 1, it, n, coeffs, it == 0 && scaled, src, dst);
+      src = dst;
+      it += n;
+    }
   }
-  return s;
+  return run_steps(pl, seq);
 }
 
 // fp32: generic kernels of tm_kernels.hip.
@@ -644,12 +829,12 @@ tm_status plan_f32(const Plan& pl, int iters, const float* coeffs, int precond) 
   const int ucfg = choose_cfg(tmk::kKindUpdate, items);
   const int part = tmk::cfg_tile(gcfg);   // row partials per Gram tile column block
 
-  if (frob) {  // Algorithm 1, first line: s = 1 / ||X0||_F
-    s = launch(pl, tmk::kKindFrob, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
-    if (s == TM_OK) s = launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob, 0);
-    if (s != TM_OK) return s;
-  }
   if (iters == 0) {
+    if (frob) {  // Algorithm 1, first line: s = 1 / ||X0||_F
+      s = launch(pl, tmk::kKindFrob, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
+      if (s == TM_OK) s = launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob, 0);
+      if (s != TM_OK) return s;
+    }
     if (from_gram) {
       s = launch(pl, tmk::kKindGram, gcfg, tmk::kSlotFirst, 0, 0.f, 0.f, 0.f, rflags | tmk::kA32, 0);
       if (s == TM_OK) s = gram_scale(pl, precond, part);
@@ -672,7 +857,7 @@ tm_status plan_f32(const Plan& pl, int iters, const float* coeffs, int precond) 
     const uint32_t scale = (first && scaled) ? tmk::kScale : 0u;
     const uint32_t gflags = (first ? rflags : 0u) | (scale ? tmk::kA32 : 0u);
     s = launch(pl, tmk::kKindGram, gcfg, src, 0, 0.f, 0.f, 0.f, gflags, 0);
-    if (s == TM_OK && first && from_gram) s = gram_scale(pl, precond, part);
+    if (s == TM_OK && first && scaled) s = first_scale(pl, precond, part);
     if (s == TM_OK) s = launch(pl, tmk::kKindPoly, pcfg, 0, 0, a, b, c, scale, 0);
     if (s == TM_OK) s = launch(pl, tmk::kKindUpdate, ucfg, src, dst, a, b, c, scale, 0);
     if (s != TM_OK) return s;
@@ -714,12 +899,15 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   int tcfg = 0;
   if (esz == 2) {
     tcfg = choose_tile_cfg(items);
+    const bool half = iters >= 2 && half_ok(iters, coeffs, precond);
     for (Item& it : items) {
       tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(tcfg)), &it.kp, &it.Np);
-      // A wide matrix that needs no padding is read in place by iteration 1;
-      // a single iteration would read and write the caller's buffer in the
-      // same launch, so it keeps the copy.
-      it.direct = !it.tall && it.kp == it.k && it.Np == it.N && iters != 1 &&
+      // A wide matrix that needs no padding is read in place by the first
+      // update; a single update would read and write the caller's buffer in
+      // the same launch, so it keeps the copy.
+      it.pair = half && pair_rule(it);
+      const int updates = it.pair ? (iters + 1) / 2 : iters;
+      it.direct = !it.tall && it.kp == it.k && it.Np == it.N && updates != 1 &&
                   (reinterpret_cast<uintptr_t>(it.x) & 15u) == 0u;
     }
   } else {
@@ -748,7 +936,7 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     s = get_workspace(dev, st, size_t(total), &pl.ws);
     if (s != TM_OK) return s;
   }
-  return esz == 2 ? plan_bf16(pl, iters, coeffs, precond, tcfg) : plan_f32(pl, iters, coeffs, precond);
+  return esz == 2 ? plan_bf16(pl, iters, coeffs, precond) : plan_f32(pl, iters, coeffs, precond);
 }
 
 tm_status run(std::vector<Item>& items, int esz, int iters, const float* coeffs, int precond,
@@ -815,6 +1003,7 @@ Item make_item(void* X, int64_t m, int64_t n, int64_t count) {
   it.x = static_cast<char*>(X);
   it.tall = m > n;
   it.direct = false;
+  it.pair = false;
   it.k = uint32_t(std::min(m, n));
   it.N = uint32_t(std::max(m, n));
   it.kp = it.k;

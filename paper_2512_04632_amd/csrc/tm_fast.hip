@@ -54,6 +54,7 @@ namespace fast {
 constexpr int kPingPongBK = 64;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
@@ -111,6 +112,10 @@ __device__ inline float bf2f(uint16_t v) { return __uint_as_float(uint32_t(v) <<
 __device__ inline uint16_t f2bf(float f) {     // v_cvt_pk_bf16_f32: round to nearest even
   __bf16 h = static_cast<__bf16>(f);
   return __builtin_bit_cast(uint16_t, h);
+}
+__device__ inline float h2f(uint16_t v) { return float(__builtin_bit_cast(_Float16, v)); }
+__device__ inline uint16_t f2h(float f) {      // v_cvt_f16_f32: round to nearest even
+  return __builtin_bit_cast(uint16_t, static_cast<_Float16>(f));
 }
 
 __device__ inline uint32_t lds_addr(const void* p) {
@@ -369,13 +374,18 @@ __device__ inline void load_frags(Frags<T>& fr, const char* sa, const char* sb, 
 // SWAP = false: acc[fm][fn] = a-rows x b-rows^T (the MFMA layout of AccT).
 // SWAP = true feeds the operands the other way round, so acc[fm][fn] holds
 // the transposed block: each lane then owns 4 consecutive columns of one row.
-template <int T, bool SWAP>
+// H: the operands are fp16 (same rate and lane layout as bf16).
+template <int T, bool SWAP, bool H>
 __device__ inline void mma(AccT<T>& acc, const Frags<T>& fr) {
 #pragma unroll
   for (int fm = 0; fm < Tile<T>::FM; ++fm)
 #pragma unroll
     for (int fn = 0; fn < Tile<T>::FN; ++fn) {
-      if constexpr (SWAP)
+      if constexpr (H)
+        acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+            __builtin_bit_cast(f16x8_t, SWAP ? fr.b[fn] : fr.a[fm]),
+            __builtin_bit_cast(f16x8_t, SWAP ? fr.a[fm] : fr.b[fn]), acc[fm][fn], 0, 0, 0);
+      else if constexpr (SWAP)
         acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
             __builtin_bit_cast(bf16x8_t, fr.b[fn]), __builtin_bit_cast(bf16x8_t, fr.a[fm]),
             acc[fm][fn], 0, 0, 0);
@@ -422,7 +432,7 @@ __device__ inline void for_each_slice(int nk, Fr& f0, Fr& f1, Slice slice) {
 // clock and compute unit) is then fed evenly instead of in one burst per stage
 // that stalls every wave.  Slices are consumed in increasing order whatever BK
 // is, so every output element accumulates the same products in the same order.
-template <int T, bool RM, bool SWAP, int BK>
+template <int T, bool RM, bool SWAP, int BK, bool H>
 __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
                                 const uint16_t* b, int64_t ldb, int K) {
   using R = Ring<T, BK>;
@@ -463,7 +473,7 @@ __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int
       if (fill)
 #pragma unroll
         for (int i = 0; i < PPS; ++i) dma_one(nx, s * PPS + i);
-      mma<T, SWAP>(acc, cur);
+      mma<T, SWAP, H>(acc, cur);
     } else {
       if (fill)
 #pragma unroll
@@ -475,7 +485,7 @@ __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int
         load_frags<T, RM, BK>(nxt, nxp, nxp + R::A_BYTES, 0, wm, wn);
       }
       __builtin_amdgcn_sched_barrier(0);
-      mma<T, SWAP>(acc, cur);
+      mma<T, SWAP, H>(acc, cur);
     }
   });
   ring_sync<0>();   // the ring is free for the epilogue
@@ -495,7 +505,7 @@ __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int
 // output element accumulates the same products in the same order as in the
 // other loops.  The producer waves return afterwards; a barrier then waits
 // only for the waves still running.
-template <int T, bool SWAP, int BK>
+template <int T, bool SWAP, int BK, bool H>
 __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
                                    const uint16_t* b, int64_t ldb, int K) {
   using R = Ring<T, BK>;
@@ -537,7 +547,7 @@ __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, 
     const char* st = stage_ptr(kt);
     if (s + 1 < NS) {
       load_frags<T, false, BK>(nxt, st, st + R::A_BYTES, s + 1, wm, wn);
-      mma<T, SWAP>(acc, cur);
+      mma<T, SWAP, H>(acc, cur);
     } else {
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): stage kt is read
@@ -547,7 +557,7 @@ __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, 
         load_frags<T, false, BK>(nxt, nxp, nxp + R::A_BYTES, 0, wm, wn);
       }
       __builtin_amdgcn_sched_barrier(0);
-      mma<T, SWAP>(acc, cur);
+      mma<T, SWAP, H>(acc, cur);
     }
   });
   return true;
@@ -576,7 +586,7 @@ __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, 
 // b(j + 1); before the barrier that ends its MEM(j), group 1 waits for its
 // a(j + 1), leaving a(j + 2) in flight: the barrier that opens group 0's
 // MEM(j + 1) comes after both.
-template <int T, bool RM, bool SWAP, int BK>
+template <int T, bool RM, bool SWAP, int BK, bool H>
 __device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
                                    const uint16_t* b, int64_t ldb, int K) {
   static_assert(Tile<T>::NW == 8, "ping-pong needs two waves per SIMD");
@@ -642,8 +652,8 @@ __device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, 
     }
     barrier_pinned();
     // COMP
-    mma<T, SWAP>(acc, f0);
-    mma<T, SWAP>(acc, f1);
+    mma<T, SWAP, H>(acc, f0);
+    mma<T, SWAP, H>(acc, f1);
     if (!g1) dma_wait<0>();
     barrier_pinned();
   }
@@ -652,18 +662,29 @@ __device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, 
   dma_wait<0>();
 }
 
-template <int T, bool RM, bool SWAP, int BK>
+// The same address in every lane, in scalar registers (the DMA's base), said
+// so that no register allocation moves it to vector ones.
+__device__ inline const uint16_t* uniform(const uint16_t* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
+  return reinterpret_cast<const uint16_t*>((uint64_t(hi) << 32) | lo);
+}
+
 // Returns false in the producer waves, which then leave the kernel.
+template <int T, bool RM, bool SWAP, int BK, bool H = false>
 __device__ inline bool run_mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
                                     const uint16_t* b, int64_t ldb, int K) {
+  a = uniform(a);
+  b = uniform(b);
   if constexpr (Tile<T>::NW == 8) {
-    mainloop_pp<T, RM, SWAP, BK>(acc, smem, a, lda, b, ldb, K);
+    mainloop_pp<T, RM, SWAP, BK, H>(acc, smem, a, lda, b, ldb, K);
     return true;
   } else if constexpr (RM) {   // the update's smaller tiles: compute waves issue the DMA
-    mainloop<T, RM, SWAP, BK>(acc, smem, a, lda, b, ldb, K);
+    mainloop<T, RM, SWAP, BK, H>(acc, smem, a, lda, b, ldb, K);
     return true;
   } else {
-    return mainloop_pc<T, SWAP, BK>(acc, smem, a, lda, b, ldb, K);
+    return mainloop_pc<T, SWAP, BK, H>(acc, smem, a, lda, b, ldb, K);
   }
 }
 
@@ -692,24 +713,47 @@ __device__ inline int xcd_remap(int p, int total) {
 }
 
 struct Loc {
-  int ent, mat, tile;
+  Entry E;
+  int mat, tile;
 };
 
+// An entry's fields in scalar registers.  Said field by field at each of the two
+// places that may supply them: joined only afterwards, the compiler would
+// choose between two addresses, and keep a copy of the descriptor in scratch
+// memory for that.
+__device__ inline Entry scalar(const Entry& e) {
+  constexpr int W = sizeof(Entry) / 4;
+  uint32_t v[W];
+  __builtin_memcpy(v, &e, sizeof(Entry));
+#pragma unroll
+  for (int i = 0; i < W; ++i) v[i] = __builtin_amdgcn_readfirstlane(v[i]);
+  Entry o;
+  __builtin_memcpy(&o, v, sizeof(Entry));
+  return o;
+}
+
 __device__ inline Loc locate(const Phase& P, int lid) {
-  // last entry whose first block is <= lid (entries without blocks share the
-  // start of the next entry and are never the last such entry)
-  int e = 0, hi = P.nent - 1;
-  while (e < hi) {
-    const int mid = (e + hi + 1) >> 1;
-    if (lid >= int(P.e[mid].tile_start)) e = mid;
-    else hi = mid - 1;
-  }
-  const int r = lid - int(P.e[e].tile_start);
-  const int per = int(P.e[e].tiles_per);
   Loc L;
-  L.ent = e;
-  L.mat = r / per;
-  L.tile = r - L.mat * per;
+  L.E = scalar(P.e[0]);   // read beside the header; most launches have one entry
+  if (P.nent > 1) {
+    // last entry whose first block is <= lid (entries without blocks share the
+    // start of the next entry and are never the last such entry)
+    int e = 0, hi = P.nent - 1;
+    while (e < hi) {
+      const int mid = (e + hi + 1) >> 1;
+      if (lid >= int(P.e[mid].tile_start)) e = mid;
+      else hi = mid - 1;
+    }
+    L.E = scalar(P.e[e]);
+  }
+  const int r = lid - int(L.E.tile_start);
+  L.mat = 0;
+  L.tile = r;
+  if (L.E.count > 1u) {
+    const int per = int(L.E.tiles_per);
+    L.mat = r / per;
+    L.tile = r - L.mat * per;
+  }
   return L;
 }
 
@@ -726,7 +770,7 @@ __device__ inline bool locate_by_matrix(const Phase& P, int p, Loc& L) {
     const int i0 = (x - (g0 & 7) + 8) & 7;        // first matrix of the entry on XCD x
     const int nt = (i0 < c ? (c - 1 - i0) / 8 + 1 : 0) * tp;
     if (j < nt) {
-      L.ent = e;
+      L.E = scalar(P.e[e]);
       L.mat = i0 + 8 * (j / tp);
       L.tile = j - (j / tp) * tp;
       return true;
@@ -757,13 +801,28 @@ __device__ inline uint16_t* wbuf(const Phase& P, const Entry& E, int mat, int sl
   return reinterpret_cast<uint16_t*>(ws_of(P, E, mat) + (w1 ? L.w1 : L.w2));
 }
 
+// One of two values; by value, since a choice between two places of a struct
+// would put a copy of it in scratch memory.
+template <class V>
+__device__ inline V pick(bool second, V a, V b) { return second ? b : a; }
+
+// A k x k buffer of the matrix whose workspace region starts at w.
+__device__ inline uint16_t* kbuf(char* w, const WsLayout& L, int slot) {
+  return reinterpret_cast<uint16_t*>(w + pick(slot == kBufA, pick(slot == kBufB, L.a32, L.b), L.a));
+}
+
+// Tile t of the upper triangle of an nb x nb grid, row by row: row I starts at
+// I (2 nb + 1 - I) / 2, solved for I in fp32 and corrected by the exact starts.
 __device__ inline void tri_tile(int t, int nb, int& I, int& J) {
-  I = 0;
-  while (t >= nb - I) {
-    t -= nb - I;
-    ++I;
-  }
-  J = I + t;
+  const float h = float(2 * nb + 1);
+  int i = int(0.5f * (h - sqrtf(fmaxf(h * h - 8.f * float(t), 0.f))));
+  i = min(max(__builtin_amdgcn_readfirstlane(i), 0), nb - 1);
+#pragma unroll 1
+  while (i > 0 && i * (2 * nb + 1 - i) / 2 > t) --i;
+#pragma unroll 1
+  while ((i + 1) * (2 * nb - i) / 2 <= t) ++i;
+  I = i;
+  J = i + t - i * (2 * nb + 1 - i) / 2;
 }
 
 // Upper tile (I, J) of a symmetric product for this block.  Normally block
@@ -777,7 +836,7 @@ __device__ inline bool sym_tile(const Phase& P, Loc& L, int& I, int& J) {
     const int sub = int(blockIdx.x) & 3;
     L = locate(P, P.tail_base + int(blockIdx.x >> 2));
     int I2, J2;
-    tri_tile(L.tile, int(P.e[L.ent].kp) / (2 * T), I2, J2);
+    tri_tile(L.tile, int(L.E.kp) / (2 * T), I2, J2);
     if (I2 == J2 && sub == 2) return false;
     I = 2 * I2 + (sub >> 1);
     J = 2 * J2 + (sub & 1);
@@ -788,7 +847,7 @@ __device__ inline bool sym_tile(const Phase& P, Loc& L, int& I, int& J) {
   } else {
     L = locate(P, xcd_remap(blockIdx.x, P.total));
   }
-  tri_tile(L.tile, int(P.e[L.ent].kp) / T, I, J);
+  tri_tile(L.tile, int(L.E.kp) / T, I, J);
   return true;
 }
 
@@ -926,14 +985,37 @@ __device__ inline void load_rows(char* st, const uint16_t* src, int64_t ld, int6
 // Symmetric-product epilogue (Gram, polynomial): value f(i_local, j_local, x,
 // staged) of C element (i, j) is written transposed into the stage as
 // (j, i); the stage then holds tile (J, I), stored as rows of block J and,
-// off the diagonal, transposed as tile (I, J).  `staged` is the stage's
-// previous bf16 at that position (the polynomial preloads A's tile (J, I)).
+// off the diagonal, transposed as tile (I, J).  f gives the 16 bits to store;
+// `staged` are the stage's previous 16 bits at that position (the polynomial
+// preloads A's tile (J, I)).
 // Each lane's 4 elements of a block are consecutive rows of one column: one
-// 8-byte stage row piece.
+// 8-byte stage row piece.  `upper` (diagonal tiles of a product whose factors
+// differ and commute only up to rounding): the elements below the diagonal are
+// the mirror of those above it there too, so that no element depends on the
+// tile size.
 template <int T, class Fv>
-__device__ inline void epilogue_sym(const AccT<T>& acc, char* st, uint16_t* D, int64_t ld, int I,
-                                    int J, Fv f) {
+__device__ __forceinline__ void epilogue_sym(const AccT<T>& acc, char* st, uint16_t* D, int64_t ld, int I,
+                                    int J, int upper, Fv f) {
   const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
+  if (upper) {
+#pragma unroll
+    for (int fm = 0; fm < Tile<T>::FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < Tile<T>::FN; ++fn) {
+        const int c = acc_col<T>(wn, fn);
+        const int r0 = acc_row<T>(wm, fm);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (r0 + u <= c) {
+            const uint16_t v = f(r0 + u, c, acc[fm][fn][u], uint16_t(0));
+            *reinterpret_cast<uint16_t*>(st + c * Stage<T>::RS + (r0 + u) * 2) = v;
+            *reinterpret_cast<uint16_t*>(st + (r0 + u) * Stage<T>::RS + c * 2) = v;
+          }
+      }
+    __syncthreads();
+    store_rows<T>(st, D, ld, int64_t(J) * T, int64_t(I) * T);
+    return;
+  }
 #pragma unroll
   for (int fm = 0; fm < Tile<T>::FM; ++fm)
 #pragma unroll
@@ -945,7 +1027,7 @@ __device__ inline void epilogue_sym(const AccT<T>& acc, char* st, uint16_t* D, i
       const uint16_t* o = reinterpret_cast<const uint16_t*>(&old);
       uint16_t out[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) out[u] = f2bf(f(r0 + u, c, acc[fm][fn][u], o[u]));
+      for (int u = 0; u < 4; ++u) out[u] = f(r0 + u, c, acc[fm][fn][u], o[u]);
       *reinterpret_cast<uint2*>(p) = *reinterpret_cast<const uint2*>(out);
     }
   __syncthreads();
@@ -960,8 +1042,9 @@ __device__ inline void epilogue_sym(const AccT<T>& acc, char* st, uint16_t* D, i
 // the first goes through the stage while the second waits in registers as
 // packed bf16, then takes the stage in a second pass.
 template <int T, class Fv>
-__device__ inline void epilogue_sym_scaled(const AccT<T>& acc, char* st, uint16_t* D, int64_t ld,
-                                           int I, int J, Fv f, const float* __restrict__ s) {
+__device__ __forceinline__ void epilogue_sym_scaled(const AccT<T>& acc, char* st, uint16_t* D, int64_t ld,
+                                           int I, int J, int upper, Fv f,
+                                           const float* __restrict__ s) {
   constexpr int FM = Tile<T>::FM, FN = Tile<T>::FN;
   const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
   uint2 keep[FM][FN];
@@ -984,10 +1067,28 @@ __device__ inline void epilogue_sym_scaled(const AccT<T>& acc, char* st, uint16_
         out[u] = f2bf(x * sv[u]);
         out2[u] = f2bf(x * sj);
       }
-      *reinterpret_cast<uint2*>(p) = *reinterpret_cast<const uint2*>(out);
+      if (!upper) {
+        *reinterpret_cast<uint2*>(p) = *reinterpret_cast<const uint2*>(out);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (r0 + u <= c) *reinterpret_cast<uint16_t*>(p + 2 * u) = out[u];
+      }
       keep[fm][fn] = *reinterpret_cast<const uint2*>(out2);
     }
     __builtin_amdgcn_sched_barrier(0);   // keeps the loads of the next block here
+  }
+  if (upper) {   // as in epilogue_sym: C[i][j] above the diagonal, from the same elements
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) {
+        const int c = acc_col<T>(wn, fn), r0 = acc_row<T>(wm, fm);
+        const uint16_t* o = reinterpret_cast<const uint16_t*>(&keep[fm][fn]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (r0 + u < c) *reinterpret_cast<uint16_t*>(st + (r0 + u) * Stage<T>::RS + c * 2) = o[u];
+      }
   }
   __syncthreads();
   store_rows<T>(st, D, ld, int64_t(J) * T, int64_t(I) * T);   // C[j][i], j in J, i in I
@@ -1027,9 +1128,9 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
   Loc L;
   int I, J;
   if (!sym_tile<T>(P, L, I, J)) return;
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int kp = int(E.kp), Np = int(E.Np);
-  const uint16_t* Y = wbuf(P, E, L.mat, P.src);
+  const uint16_t* Y = wbuf(P, E, L.mat, Ops(E.flags).src());
   char* w = ws_of(P, E, L.mat);
   const WsLayout WL = ws_layout(E.kp, E.Np, 2);
   const int64_t ldy = WL.ldy;
@@ -1039,8 +1140,12 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
   if (P.flags & kA32) {
     store_sym_f32<T>(acc, reinterpret_cast<float*>(w + WL.a32), kp, I, J);
   } else {
-    auto f = [](int, int, float x, uint16_t) { return x; };
-    epilogue_sym<T>(acc, smem, reinterpret_cast<uint16_t*>(w + WL.a), WL.ldg, I, J, f);
+    uint16_t* A = reinterpret_cast<uint16_t*>(w + WL.a);
+    if (E.flags & kPair)
+      epilogue_sym<T>(acc, smem, A, WL.ldg, I, J, 0,
+                      [](int, int, float x, uint16_t) { return f2h(x * kScaleA); });
+    else
+      epilogue_sym<T>(acc, smem, A, WL.ldg, I, J, 0, [](int, int, float x, uint16_t) { return f2bf(x); });
   }
 
   // The host never asks a 32 tile for row sums (their partials cover 64 columns).
@@ -1098,35 +1203,59 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
   }
 }
 
-// B~ = b A + c A A + a I (upper tiles, mirrored).  The stage is preloaded with
-// A's tile (J, I), whose element (j, i) equals A_ij.
-template <int T, int BK, bool SCALED>
-__global__ __launch_bounds__(Tile<T>::NTT) void k_poly_fast(const Phase P) {
+// One k x k product of the iteration, out = alpha L R + beta M + gamma I over
+// the upper tiles, mirrored (Ops): the polynomial B~ = b A + c A A + a I,
+// and for two iterations per update T = B~ A, A' = B~ T (the next Gram, since
+// B~ and A commute: B~ A B~ = (B~ Y)(B~ Y)^T) and Q = B~' B~.  L and R are
+// symmetric, so R's rows are the columns that the product needs.  The stage is
+// preloaded with M's tile (J, I), whose element (j, i) equals M_ij.  MODE: SymMode;
+// H: fp16 operands.
+template <int T, int BK, int MODE, bool H>
+__device__ __forceinline__ void sym_block(const Phase& P, const Entry& E, char* smem, char* w, int I,
+                                          int J) {
+  const Ops op(E.flags);
+  const int kp = int(E.kp);
+  const WsLayout WL = ws_layout(E.kp, E.Np, 2);
+  const int64_t ldg = WL.ldg;
+  AccT<T> acc;
+  if (!run_mainloop<T, false, false, BK, H>(acc, smem, kbuf(w, WL, op.l()) + int64_t(I) * T * ldg, ldg,
+                                            kbuf(w, WL, op.r()) + int64_t(J) * T * ldg, ldg, kp))
+    return;
+  const int hasm = !H || op.m() != kNoBuf;
+  if (hasm) load_rows<T>(smem, kbuf(w, WL, op.m()), ldg, int64_t(J) * T, int64_t(I) * T);
+  __syncthreads();
+  const bool pair = (E.flags & kPair) != 0u;
+  const float ga = pick(pair, P.a, P.a2), be = pick(pair, P.b, P.b2), al = pick(pair, P.c, P.c2);
+  const int diag = I == J, upper = H && diag && op.l() != op.r();   // factors differ in pairs only
+  uint16_t* out = kbuf(w, WL, op.out());
+  auto val = [=](int i, int j, float x, uint16_t mij) __attribute__((always_inline)) {
+    const float m = hasm ? (H ? h2f(mij) : bf2f(mij)) : 0.f;
+    // spelled out, so that every kernel that forms B~ rounds it alike
+    return __builtin_fmaf(be, m, al * x) + ((diag && i == j) ? ga : 0.f);
+  };
+  if constexpr (MODE == kSymBf16Scaled || MODE == kSymFactorScaled)
+    epilogue_sym_scaled<T>(acc, smem, out, ldg, I, J, upper, val, reinterpret_cast<const float*>(w + WL.s));
+  else
+    epilogue_sym<T>(acc, smem, out, ldg, I, J, upper,
+                    [=](int i, int j, float x, uint16_t mij) __attribute__((always_inline)) {
+                      const float v = val(i, j, x, mij);
+                      return H && MODE != kSymFactor ? f2h(v) : f2bf(v);
+                    });
+}
+
+template <int T, int BK, int MODE>
+__global__ __launch_bounds__(Tile<T>::NTT) void k_sym_fast(const Phase P) {
   __shared__ __attribute__((aligned(1024))) char smem[smem_bytes<T, BK>()];
-  constexpr int FM = Tile<T>::FM, FN = Tile<T>::FN;
   Loc L;
   int I, J;
   if (!sym_tile<T>(P, L, I, J)) return;
-  const Entry& E = P.e[L.ent];
-  const int kp = int(E.kp);
-  char* w = ws_of(P, E, L.mat);
-  const WsLayout WL = ws_layout(E.kp, E.Np, 2);
-  const uint16_t* A = reinterpret_cast<const uint16_t*>(w + WL.a);
-  uint16_t* B = reinterpret_cast<uint16_t*>(w + WL.b);
-  const int64_t ldg = WL.ldg;
-  AccT<T> acc;
-  if (!run_mainloop<T, false, false, BK>(acc, smem, A + int64_t(I) * T * ldg, ldg, A + int64_t(J) * T * ldg, ldg, kp)) return;
-  load_rows<T>(smem, A, ldg, int64_t(J) * T, int64_t(I) * T);
-  __syncthreads();
-  const float a = P.a, b = P.b, c = P.c;
-  const bool diag = I == J;
-  auto f = [=](int i, int j, float x, uint16_t aij) {
-    return b * bf2f(aij) + c * x + ((diag && i == j) ? a : 0.f);
-  };
-  if constexpr (SCALED)   // kScale: a separate kernel, so that neither epilogue spills
-    epilogue_sym_scaled<T>(acc, smem, B, ldg, I, J, f, reinterpret_cast<const float*>(w + WL.s));
-  else
-    epilogue_sym<T>(acc, smem, B, ldg, I, J, f);
+  char* w = ws_of(P, L.E, L.mat);
+  if constexpr (MODE == kSymMixed) {
+    if (L.E.flags & kPair) sym_block<T, BK, MODE, true>(P, L.E, smem, w, I, J);
+    else sym_block<T, BK, MODE, false>(P, L.E, smem, w, I, J);
+  } else {
+    sym_block<T, BK, MODE, (MODE >= kSymHalf)>(P, L.E, smem, w, I, J);
+  }
 }
 
 // Y' = B~ Y.  The operands are fed transposed so that each lane holds 4
@@ -1148,7 +1277,7 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
   if (tail) L = locate(P, P.tail_base + int(blockIdx.x) / FF);
   else if (!(P.flags & kByMatrix)) L = locate(P, xcd_remap(blockIdx.x, P.total));
   else if (!locate_by_matrix(P, int(blockIdx.x), L)) return;
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int kp = int(E.kp), Np = int(E.Np), k = int(E.k), N = int(E.N);
   const int TL = F * T;
   const int nI = kp / TL, nL = Np / TL;
@@ -1163,8 +1292,10 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
 
   char* w = ws_of(P, E, L.mat);
   const WsLayout WL = ws_layout(E.kp, E.Np, 2);
-  const uint16_t* B = reinterpret_cast<const uint16_t*>(w + WL.b);
-  const uint16_t* Y = wbuf(P, E, L.mat, P.src);
+  const Ops op(E.flags);
+  const int dst = op.dst();
+  const uint16_t* B = kbuf(w, WL, op.fac());
+  const uint16_t* Y = wbuf(P, E, L.mat, op.src());
   const int64_t ldg = WL.ldg, ldy = WL.ldy;
   AccT<T> acc;
   run_mainloop<T, true, true, BK>(acc, smem, B + int64_t(I) * T * ldg, ldg, Y + int64_t(Lb) * T, ldy, kp);
@@ -1186,8 +1317,8 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
       *reinterpret_cast<uint2*>(smem + i * Stage<T>::RS + l0 * 2) = *reinterpret_cast<const uint2*>(out);
     }
   __syncthreads();
-  if (P.dst != kSlotFinal)
-    store_rows<T>(smem, wbuf(P, E, L.mat, P.dst), ldy, int64_t(I) * T, int64_t(Lb) * T);
+  if (dst != kSlotFinal)
+    store_rows<T>(smem, wbuf(P, E, L.mat, dst), ldy, int64_t(I) * T, int64_t(Lb) * T);
   else if ((E.flags & kTall) == 0u)
     store_rows_user<T>(smem, user_of(P, E, L.mat), k, N, I * T, Lb * T);
   else
@@ -1203,7 +1334,7 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
 __global__ __launch_bounds__(256) void k_load_in(const Phase P) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[kTransposeTile][kTransposeTile + 2];
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int k = int(E.k), N = int(E.N);
   const int64_t ldy = ws_layout(E.kp, E.Np, 2).ldy;
   const int nI = int(E.kp) / kTransposeTile;
@@ -1260,7 +1391,8 @@ __global__ __launch_bounds__(256) void k_load_in(const Phase P) {
   }
 }
 
-// First iteration after the scaling: A1 = bf16(s_i A0_ij s_j).  The Gram
+// First iteration after the scaling: A1 = s_i A0_ij s_j, rounded once (bf16, or
+// fp16 for a kPair entry).  The Gram
 // stored A0 (fp32) as its upper tiles only, which contain every upper 64 x 64
 // tile whatever its tile size; one block per upper 64 x 64 tile (I <= J)
 // reads it once and writes A1's tile (I, J) and, off the diagonal, its
@@ -1272,7 +1404,7 @@ __global__ __launch_bounds__(256) void k_apply_s(const Phase P) {
   __shared__ uint16_t tt[64][64 + 2];
   __shared__ float sv[128];   // s of the tile's 64 rows, then of its 64 columns
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int kp = int(E.kp);
   char* w = ws_of(P, E, L.mat);
   const WsLayout WL = ws_layout(E.kp, E.Np, 2);
@@ -1306,14 +1438,18 @@ __global__ __launch_bounds__(256) void k_apply_s(const Phase P) {
   const float si = sv[r];
   const float* src = A0 + int64_t(i) * kp + j0;
   uint16_t o[16];
+  auto round = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4 v = *reinterpret_cast<const float4*>(src + 4 * q);
-    o[4 * q + 0] = f2bf(v.x * (si * sv[64 + c0 + 4 * q + 0]));
-    o[4 * q + 1] = f2bf(v.y * (si * sv[64 + c0 + 4 * q + 1]));
-    o[4 * q + 2] = f2bf(v.z * (si * sv[64 + c0 + 4 * q + 2]));
-    o[4 * q + 3] = f2bf(v.w * (si * sv[64 + c0 + 4 * q + 3]));
-  }
+    for (int q = 0; q < 4; ++q) {
+      const float4 v = *reinterpret_cast<const float4*>(src + 4 * q);
+      o[4 * q + 0] = f(v.x * (si * sv[64 + c0 + 4 * q + 0]));
+      o[4 * q + 1] = f(v.y * (si * sv[64 + c0 + 4 * q + 1]));
+      o[4 * q + 2] = f(v.z * (si * sv[64 + c0 + 4 * q + 2]));
+      o[4 * q + 3] = f(v.w * (si * sv[64 + c0 + 4 * q + 3]));
+    }
+  };
+  if (E.flags & kPair) round([](float x) { return f2h(x * kScaleA); });
+  else round([](float x) { return f2bf(x); });
   uint16_t* dst = A + int64_t(i) * WL.ldg + j0;
   reinterpret_cast<uint4*>(dst)[0] = reinterpret_cast<const uint4*>(o)[0];
   reinterpret_cast<uint4*>(dst)[1] = reinterpret_cast<const uint4*>(o)[1];
@@ -1338,8 +1474,15 @@ static hipError_t launch_t(int kind, const Phase& P, hipStream_t st) {
   switch (kind) {
     case kKindGram: TM_LAUNCH((k_gram_fast<T, BK>));
     case kKindPoly:
-      if (P.flags & kScale) TM_LAUNCH((k_poly_fast<T, BK, true>));
-      TM_LAUNCH((k_poly_fast<T, BK, false>));
+      switch (P.symmode) {
+        case kSymBf16: TM_LAUNCH((k_sym_fast<T, BK, kSymBf16>));
+        case kSymBf16Scaled: TM_LAUNCH((k_sym_fast<T, BK, kSymBf16Scaled>));
+        case kSymHalf: TM_LAUNCH((k_sym_fast<T, BK, kSymHalf>));
+        case kSymFactor: TM_LAUNCH((k_sym_fast<T, BK, kSymFactor>));
+        case kSymFactorScaled: TM_LAUNCH((k_sym_fast<T, BK, kSymFactorScaled>));
+        case kSymMixed: TM_LAUNCH((k_sym_fast<T, BK, kSymMixed>));
+      }
+      break;
     case kKindUpdate:
       if constexpr (T >= 64) {   // layout tiles only; no producer waves
         hipLaunchKernelGGL((k_update_fast<T, BK>), dim3(P.total), dim3(Tile<T>::NT), 0, st, P);

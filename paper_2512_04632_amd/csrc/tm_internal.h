@@ -2,6 +2,7 @@
 // (tm_kernels.hip): launch descriptors and the per-matrix workspace layout.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifndef __HIPCC__
@@ -56,6 +57,7 @@ constexpr uint32_t kTail = 128u;  // matrix-core kernels: blocks are 2 x 2 sub-t
 constexpr uint32_t kTail4 = 512u; // with kTail (update only): 4 x 4 sub-tiles of a quarter size
 constexpr uint32_t kByMatrix = 1024u; // matrix-core kernels: XCD x runs every tile of the launch's
                                       // matrices x, x + 8, ... (blocks p with p % 8 == x)
+constexpr uint32_t kTrace = 4096u;   // with kFrob: s = (trace of the first Gram)^(-1/2)
 constexpr uint32_t kFuseS = 256u; // bf16 rescale of A0: the AOL vector is summed in the same
                                   // kernel from the Gram's row partials (aux columns each)
 
@@ -65,6 +67,39 @@ constexpr uint32_t kDirect = 2u;  // bf16: the user matrix already has the padde
                                   // dims multiples of the tile, 16-byte aligned); iteration 1
                                   // reads it in place of the W1 copy
 constexpr uint32_t kPtrTab = 4u;  // matrix j's user pointer is xp[xbase + j] of the launch
+constexpr uint32_t kPair = 8u;    // bf16: two iterations per update (Phase's second set of coefficients)
+
+// The k x k matrices of a kPair entry are fp16 (but the update's factor), A
+// and T scaled by kScaleA and B~ by kScaleB (powers of two: no rounding): |A_ij| <= sigma_max^2 and |B~_ij| <= max |a + b x + c x^2| stay far
+// below 65504 / scale (the host checks the bounds per call), and the small
+// off-diagonal entries of large Gram matrices stay normal.
+constexpr float kScaleA = 4096.f;
+constexpr float kScaleB = 1024.f;
+
+// The k x k buffers of a matrix: A, B and T, which shares the fp32 first
+// Gram's memory (dead once it has been rescaled).
+constexpr int kBufA = 0, kBufB = 1, kBufT = 2;
+
+// Operands of a bf16 matrix-core step, packed into Entry::flags from bit
+// kOpsShift on (two bits each): the Y slots read and written, the k x k factor
+// of an update, and of a k x k product out = alpha L R + beta M + gamma I (all
+// symmetric, upper tiles mirrored) the buffers L, R, M (kNoBuf: no M) and out.
+constexpr int kNoBuf = 3;
+constexpr int kOpsShift = 8;
+TM_HD uint32_t pack_ops(int src, int dst, int fac, int l, int r, int m, int out) {
+  return uint32_t(src | dst << 2 | fac << 4 | l << 6 | r << 8 | m << 10 | out << 12) << kOpsShift;
+}
+struct Ops {
+  uint32_t v;
+  TM_HD explicit Ops(uint32_t flags) : v(flags >> kOpsShift) {}
+  TM_HD int src() const { return int(v & 3u); }
+  TM_HD int dst() const { return int(v >> 2 & 3u); }
+  TM_HD int fac() const { return int(v >> 4 & 3u); }
+  TM_HD int l() const { return int(v >> 6 & 3u); }
+  TM_HD int r() const { return int(v >> 8 & 3u); }
+  TM_HD int m() const { return int(v >> 10 & 3u); }
+  TM_HD int out() const { return int(v >> 12 & 3u); }
+};
 
 constexpr int kFrobBlocks = 32;   // partial sums of squares per matrix
 constexpr int kMinTile = 64;      // smallest Gram tile: bounds the row-sum partial count
@@ -75,25 +110,42 @@ struct Entry {
   uint32_t k, N;       // wide view: k = min(m, n) rows, N = max(m, n) columns
   uint32_t kp, Np;     // padded workspace dims: rows of Y, A, B and ld of A, B (kp); ld of Y (Np)
   uint32_t count;      // matrices in this entry
-  uint32_t flags;      // kTall, kDirect, kPtrTab
+  uint32_t flags;      // kTall, kDirect, kPtrTab, kPair; packed operands (Ops)
   uint32_t tile_start; // first logical block of this entry in the launch
   uint32_t tiles_per;  // blocks per matrix in the launch
   uint32_t xbase;      // with kPtrTab: first pointer of this entry in xp
 };
 
+// Types of a launch of k x k products (Phase::symmode).
+enum SymMode {
+  kSymBf16,        // bf16 throughout (step by step)
+  kSymBf16Scaled,  // the same, out times diag(s): a kernel of its own, so that neither
+                   // epilogue spills
+  kSymHalf,        // fp16 throughout; the power-of-two scales ride on alpha, beta, gamma
+  kSymFactor,      // fp16 factors, bf16 out
+  kSymFactorScaled,
+  kSymMixed        // entries of both classes: kSymHalf for kPair, else kSymBf16
+};
+
+// What every block reads first is one 64-byte line, and the first entry the
+// next: a launch of a dependent chain spends a good part of its few
+// microseconds on these reads, so they are few and independent of each other
+// (spread over four lines, one 768 x 3072 matrix's 13 launches took 7 us more).
 struct Phase {
-  Entry e[kMaxEntries];
   char* ws;            // workspace base
   int32_t nent;
   int32_t total;       // logical blocks in the launch
-  int32_t src, dst;    // Y slots
-  float a, b, c;       // coefficients of this iteration
   uint32_t flags;
-  int32_t aux;         // AOL-vector / partial kernels: columns per row partial of the Gram
   int32_t tail_base;   // with kTail: first logical tile (of size 2T) covered by the launch
+  int32_t aux;         // AOL-vector / partial kernels: columns per row partial of the Gram
+  int32_t src, dst;    // Y slots (fp32 path)
+  float a, b, c;       // fp32 path: coefficients of this iteration; bf16 k x k products:
+  float a2, b2, c2;    // gamma, beta, alpha of the entries without, with kPair
+  int32_t symmode;     // k x k products: SymMode
+  Entry e[kMaxEntries];
   char* xp[kMaxPtrs];  // user matrices of the kPtrTab entries
 };
-static_assert(sizeof(Entry) == 48 && sizeof(Phase) <= 3200, "kernel arguments of one launch");
+static_assert(offsetof(Phase, e) == 64 && sizeof(Entry) == 48 && sizeof(Phase) <= 3200, "kernel arguments of one launch");
 
 // Fused small-matrix path (bf16, every matrix of the call with k <= 128 and
 // its zero-padded Y, A and B within the LDS): one workgroup per matrix runs

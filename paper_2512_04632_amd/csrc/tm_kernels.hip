@@ -75,24 +75,47 @@ __device__ inline int xcd_remap(int p, int total) {
 }
 
 struct Loc {
-  int ent, mat, tile;
+  Entry E;
+  int mat, tile;
 };
 
+// An entry's fields in scalar registers.  Said field by field at each of the two
+// places that may supply them: joined only afterwards, the compiler would
+// choose between two addresses, and keep a copy of the descriptor in scratch
+// memory for that.
+__device__ inline Entry scalar(const Entry& e) {
+  constexpr int W = sizeof(Entry) / 4;
+  uint32_t v[W];
+  __builtin_memcpy(v, &e, sizeof(Entry));
+#pragma unroll
+  for (int i = 0; i < W; ++i) v[i] = __builtin_amdgcn_readfirstlane(v[i]);
+  Entry o;
+  __builtin_memcpy(&o, v, sizeof(Entry));
+  return o;
+}
+
 __device__ inline Loc locate(const Phase& P, int lid) {
-  // last entry whose first block is <= lid (entries without blocks share the
-  // start of the next entry and are never the last such entry)
-  int e = 0, hi = P.nent - 1;
-  while (e < hi) {
-    const int mid = (e + hi + 1) >> 1;
-    if (lid >= int(P.e[mid].tile_start)) e = mid;
-    else hi = mid - 1;
-  }
-  const int r = lid - int(P.e[e].tile_start);
-  const int per = int(P.e[e].tiles_per);
   Loc L;
-  L.ent = e;
-  L.mat = r / per;
-  L.tile = r - L.mat * per;
+  L.E = scalar(P.e[0]);   // read beside the header; most launches have one entry
+  if (P.nent > 1) {
+    // last entry whose first block is <= lid (entries without blocks share the
+    // start of the next entry and are never the last such entry)
+    int e = 0, hi = P.nent - 1;
+    while (e < hi) {
+      const int mid = (e + hi + 1) >> 1;
+      if (lid >= int(P.e[mid].tile_start)) e = mid;
+      else hi = mid - 1;
+    }
+    L.E = scalar(P.e[e]);
+  }
+  const int r = lid - int(L.E.tile_start);
+  L.mat = 0;
+  L.tile = r;
+  if (L.E.count > 1u) {
+    const int per = int(L.E.tiles_per);
+    L.mat = r / per;
+    L.tile = r - L.mat * per;
+  }
   return L;
 }
 
@@ -409,7 +432,7 @@ __global__ __launch_bounds__(256) void k_gram(const Phase P) {
   __shared__ __attribute__((aligned(16))) char smem[C::LDS];
   static_assert(C::BM == C::BN, "square tiles");
   const Loc L = locate(P, xcd_remap(blockIdx.x, P.total));
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int k = int(E.k), N = int(E.N);
   int I, J;
   tri_tile(L.tile, int(cdiv(E.k, C::BM)), I, J);
@@ -475,7 +498,7 @@ template <typename T, class C, bool SCALE>
 __global__ __launch_bounds__(256) void k_poly(const Phase P) {
   __shared__ __attribute__((aligned(16))) char smem[C::LDS];
   const Loc L = locate(P, xcd_remap(blockIdx.x, P.total));
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int k = int(E.k);
   int I, J;
   tri_tile(L.tile, int(cdiv(E.k, C::BM)), I, J);
@@ -517,7 +540,7 @@ template <typename T, class C, bool SCALE>
 __global__ __launch_bounds__(256) void k_update(const Phase P) {
   __shared__ __attribute__((aligned(16))) char smem[C::LDS];
   const Loc L = locate(P, xcd_remap(blockIdx.x, P.total));
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int k = int(E.k), N = int(E.N);
   // Tiles ordered in groups of 4 block rows so concurrent tiles share B rows.
   const int nI = int(cdiv(E.k, C::BM)), nL = int(cdiv(E.N, C::BN));
@@ -569,7 +592,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_transpose_in(const Phase P) {
   __shared__ T tile[kTransposeTile][kTransposeTile + 1];
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int k = int(E.k), N = int(E.N);
   const int nI = int(cdiv(E.k, kTransposeTile));
   const int ti = L.tile % nI, tl = L.tile / nI;
@@ -602,7 +625,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_frob_partial(const Phase P) {
   __shared__ float red[4];
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const bool from_part = (P.flags & kFromPart) != 0u;
   // partials past column k are zero: their count follows k, not the padding,
   // so the chunks (and the sum) do not depend on the tile size
@@ -634,20 +657,34 @@ __global__ __launch_bounds__(256) void k_frob_partial(const Phase P) {
 
 // s_i = 1/sqrt(sum_Jb part[Jb][i]) (0 for a zero sum), or with kFrob the
 // uniform 1/sqrt(sum of the Frobenius partials), with kFrob | kS4 the uniform
-// (sum of the partials)^(-1/4).  Fixed summation order.
+// (sum of the partials)^(-1/4).  With kFrob | kTrace the uniform scale comes
+// from ||X||_F^2 = tr(A0): the k diagonal elements of the fp32 first Gram in
+// place of a pass over X (one 768 x 3072 matrix: 70 us for the partials of 32
+// blocks, 4 us for the trace), every block adding all of them in the same
+// order.  Fixed summation order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_aol_vector(const Phase P) {
+  __shared__ float red[4];
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int k = int(E.k), kp = int(E.kp);
   const int i = L.tile * 256 + int(threadIdx.x);
-  if (i >= kp) return;
   char* w = ws_of<T>(P, E, L.mat);
   const WsLayout WL = ws_layout(E.kp, E.Np, sizeof(T));
   float* s = reinterpret_cast<float*>(w + WL.s);
+  float tr = 0.f;
+  if (P.flags & kTrace) {
+    const float* A0 = reinterpret_cast<const float*>(w + WL.a32);
+#pragma unroll 8
+    for (int q = int(threadIdx.x); q < k; q += 256) tr += A0[int64_t(q) * (kp + 1)];
+    tr = block_sum_256(tr, red);
+  }
+  if (i >= kp) return;
   float r = 0.f;
   if (i < k) {
-    if (P.flags & kFrob) {
+    if (P.flags & kTrace) {
+      r = tr;
+    } else if (P.flags & kFrob) {
       const float* fp = reinterpret_cast<const float*>(w + WL.fpart);
 #pragma unroll 8
       for (int b = 0; b < kFrobBlocks; ++b) r += fp[b];
@@ -667,7 +704,7 @@ __global__ __launch_bounds__(256) void k_aol_vector(const Phase P) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_apply_scale(const Phase P) {
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int64_t total = int64_t(E.k) * E.N;
   T* X = user_of<T>(P, E, L.mat);
   const float* s = reinterpret_cast<const float*>(ws_of<T>(P, E, L.mat) +
@@ -685,7 +722,7 @@ __global__ __launch_bounds__(256) void k_apply_scale(const Phase P) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_copy_out(const Phase P) {
   const Loc L = locate(P, blockIdx.x);
-  const Entry& E = P.e[L.ent];
+  const Entry& E = L.E;
   const int64_t total = int64_t(E.k) * E.N;
   const T* S = slot_ptr<T>(P, E, L.mat, P.src);
   T* D = user_of<T>(P, E, L.mat);

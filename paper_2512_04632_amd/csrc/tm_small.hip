@@ -17,9 +17,10 @@
 //   * AOL row sums: 16-column blocks reduced with the butterfly pairing of
 //     index bits 0..3, four of them added as (b0 + b1) + (b2 + b3) into the
 //     64-column partials, the partials added in order; s = 1 / sqrt(sum);
-//   * Frobenius: 32 chunks of the stored matrix, each summed by 256 threads
-//     strided by 256 and reduced across lanes and waves, then added in order;
-//     Schatten-4: the same chunking over the 64-column partials of A0^2;
+//   * Frobenius: the trace of A0, a diagonal element per thread, reduced across
+//     lanes and waves; Schatten-4: the 64-column partials of A0^2 in 32 chunks,
+//     each summed by 256 threads strided by 256, reduced across lanes and waves,
+//     then added in order;
 //   * A1 = bf16(A0_ij (s_i s_j)), the first polynomial stores
 //     C = bf16(B~_ij s_j) and the first update computes C X0; every other
 //     stored A, B~ and Y is rounded once to bf16.
@@ -454,13 +455,13 @@ __device__ inline float part64(const Geo& G, int b, int i) {
 }
 
 // Sum of `total` terms in 32 chunks, as the tiled path's partial kernels form
-// it: within a chunk thread t adds terms lo + t, lo + t + 256, ... in order
-// (x += v * v with SQ, else x += v), the 64 lanes of a wave are reduced by the
-// xor butterfly over offsets 32, 16, ..., 1 and the four wave sums added in
-// order; the chunk sums are then added in order.  Every thread forms its sums
+// it: within a chunk thread t adds terms lo + t, lo + t + 256, ... in order,
+// the 64 lanes of a wave are reduced by the xor butterfly over offsets 32, 16,
+// ..., 1 and the four wave sums added in order; the chunk sums are then added
+// in order.  Every thread forms its sums
 // of CG chunks (LB terms read before they are added), then their CG
 // butterflies run side by side.  Only the first 256 threads take part.
-template <bool SQ, class V>
+template <class V>
 __device__ inline float chunked_sum(const Geo& G, uint32_t total, V term) {
   constexpr int CG = 8;                          // chunks reduced side by side
   const uint32_t chunk = (total + kFrobBlocks - 1) / kFrobBlocks;
@@ -480,10 +481,7 @@ __device__ inline float chunked_sum(const Geo& G, uint32_t total, V term) {
           e[u] = qq < hi ? e[u] : 0.f;
         }
 #pragma unroll
-        for (int u = 0; u < LB; ++u) {
-          if constexpr (SQ) x[j] += e[u] * e[u];   // +0 for the terms past the chunk
-          else x[j] += e[u];
-        }
+        for (int u = 0; u < LB; ++u) x[j] += e[u];   // +0 for the terms past the chunk
       }
     }
 #pragma unroll
@@ -526,19 +524,6 @@ __global__ __launch_bounds__(64 * NW) void k_small_ns(const SmallPhase P) {
   load_y<NT>(G, X, tall);
   __syncthreads();
 
-  // Frobenius scale (Algorithm 1), over the elements of X in its storage order
-  float s_uniform = 0.f;
-  if (precond == TM_PRECOND_FROBENIUS) {
-    const int d = tall ? G.k : G.N;
-    const Div dv{uint32_t(d)};
-    const float r = chunked_sum<true>(G, uint32_t(G.k * G.N), [&](uint32_t q) {
-      const int r0 = int(dv(q)), c0 = int(q) - r0 * d;   // X[r0][c0]
-      const int i = tall ? c0 : r0, l = tall ? r0 : c0;
-      return bf2f(*reinterpret_cast<const uint16_t*>(G.y + i * G.ry + l * 2));
-    });
-    s_uniform = r >= kTiny ? 1.0f / sqrtf(r) : 0.f;
-  }
-
   f32x4_t acc[F][F];
   for (int it = 0; it < P.iters; ++it) {
     const float ca = P.coef[it][0], cb = P.coef[it][1], cc = P.coef[it][2];
@@ -549,6 +534,26 @@ __global__ __launch_bounds__(64 * NW) void k_small_ns(const SmallPhase P) {
       if (first && from_gram) row_sums16<F>(G, acc, precond == TM_PRECOND_SCHATTEN4);
     }
     if (first && scaled) {
+      float s_uniform = 0.f;
+      if (precond == TM_PRECOND_FROBENIUS) {   // ||X||_F^2 = tr(A0) (Algorithm 1)
+        if (prod) {
+#pragma unroll
+          for (int fm = 0; fm < F; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < F; ++fn)
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (row0<F>(fm) + u == col0<F>(fn)) G.rs[col0<F>(fn)] = acc[fm][fn][u];
+        }
+        __syncthreads();
+        float x = int(threadIdx.x) < G.k ? G.rs[threadIdx.x] : 0.f;   // k <= 128: one term a thread
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+        if (lane == 0 && prod) G.red[w] = x;
+        __syncthreads();
+        const float r = G.red[0] + G.red[1] + G.red[2] + G.red[3];
+        s_uniform = r >= kTiny ? 1.0f / sqrtf(r) : 0.f;
+      }
       if (from_gram) {
         __syncthreads();
         const int nb = (G.k + 63) / 64;   // 64-column partials per row
@@ -561,7 +566,7 @@ __global__ __launch_bounds__(64 * NW) void k_small_ns(const SmallPhase P) {
           }
         } else {   // ||X||_S4 = ||A0||_F^(1/2) from the partials of A0_ij^2
           const Div dk{uint32_t(G.k)};
-          const float r = chunked_sum<false>(G, uint32_t(nb * G.k), [&](uint32_t q) {
+          const float r = chunked_sum(G, uint32_t(nb * G.k), [&](uint32_t q) {
             const int b = int(dk(q)), i = int(q) - b * G.k;
             return part64(G, b, i);
           });
@@ -604,7 +609,7 @@ __global__ __launch_bounds__(64 * NW) void k_small_ns(const SmallPhase P) {
           uint16_t o[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const float x = cb * bf2f(av[u]) + cc * acc[fm][fn][u] + (i0 + u == j ? ca : 0.f);
+            const float x = __builtin_fmaf(cb, bf2f(av[u]), cc * acc[fm][fn][u]) + (i0 + u == j ? ca : 0.f);
             // stored at (j, i0 + u): B~ is symmetric; C[j][i] = B~_ij s_i
             o[u] = f2bf(first && scaled ? x * G.s[i0 + u] : x);
           }
