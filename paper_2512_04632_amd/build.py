@@ -2,7 +2,7 @@
 
     python -m paper_2512_04632_amd.build
 
-The bf16 and fp32 kernel sets are compiled as two translation units in
+The bf16 and fp32 kernel sets are compiled as translation units of their own in
 parallel with the host planner, then linked into one shared library next to
 this file.
 """
@@ -47,6 +47,7 @@ def build(verbose: bool = False) -> str:
             (os.path.join(CSRC, "tm_kernels.hip"), ["-DTM_ELEM_BYTES=2"], "k_bf16.o"),
             (os.path.join(CSRC, "tm_kernels.hip"), ["-DTM_ELEM_BYTES=4"], "k_f32.o"),
             (os.path.join(CSRC, "tm_fast.hip"), [], "k_fast.o"),
+            (os.path.join(CSRC, "tm_fast.hip"), ["-DTM_SPLIT=1"], "k_split.o"),
             (os.path.join(CSRC, "tm_optim.hip"), [], "k_optim.o"),
             (os.path.join(CSRC, "tm_noalloc.hip"), [], "noalloc.o"),
             (os.path.join(CSRC, "tm_small.hip"), [], "k_small.o"),

@@ -21,6 +21,7 @@
 namespace tmk {
 hipError_t launch_elementwise_bf16(int kind, const Phase& P, hipStream_t st);
 hipError_t launch_fast_bf16(int kind, int cfg, int step, const Phase& P, hipStream_t st);
+hipError_t launch_split_f32(int kind, int cfg, int step, const Phase& P, hipStream_t st);
 hipError_t launch_phase_f32(int kind, int cfg, const Phase& P, hipStream_t st);
 hipError_t launch_opt(int apply, const OptPhase& P, hipStream_t st);
 hipError_t launch_small_bf16(int F, int big, const SmallPhase& P, hipStream_t st);
@@ -234,6 +235,7 @@ struct Plan {
   int esz;
   hipStream_t st;
   int tcfg = 0;                   // bf16: the call's layout tile
+  bool split = false;             // fp32 on fp16 planes (tm_fast.hip's kernels)
   bool timed = true;              // the timing hooks may bracket this call's launches
 };
 
@@ -283,10 +285,14 @@ tm_status fire(const Plan& pl, int kind, int cfg, const Phase& P) {
   }
   if (P.total <= 0) return TM_OK;
   hipError_t e;
-  if (pl.esz == 4)
+  const bool elementwise =
+      kind == tmk::kKindFrob || kind == tmk::kKindAolVector || kind == tmk::kKindApplyScale;
+  if (pl.esz == 4 && (!pl.split || elementwise))
     e = tmk::launch_phase_f32(kind, cfg, P, pl.st);
-  else if (kind == tmk::kKindFrob || kind == tmk::kKindAolVector || kind == tmk::kKindApplyScale)
+  else if (elementwise)
     e = tmk::launch_elementwise_bf16(kind, P, pl.st);
+  else if (pl.split)
+    e = tmk::launch_split_f32(kind, cfg, k_step(kind, cfg, P), P, pl.st);
   else
     e = tmk::launch_fast_bf16(kind, cfg, k_step(kind, cfg, P), P, pl.st);
   if (tl.start) {
@@ -446,7 +452,7 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     // few matrices keeps the chunks.
     const bool mc0 = kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate;
     bool by_matrix = false;
-    if (pl.esz == 2 && mc0) {
+    if ((pl.esz == 2 || pl.split) && mc0) {
       uint32_t kmin = UINT32_MAX, kmax = 0;
       for (int e = 0; e < P.nent; ++e) {
         if (P.e[e].tiles_per == 0u) continue;
@@ -487,7 +493,7 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     // (same per-element arithmetic, four times the blocks for the idle units);
     // an update tail of at most 16 tiles as 4 x 4 sub-tiles of 64 x 64.
     const bool mc = kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate;
-    const int tail = (!by_matrix && pl.esz == 2 && ccfg == 0 && mc && P.total > kWave && P.total % kWave <= kWave / 4)
+    const int tail = (!by_matrix && (pl.esz == 2 || pl.split) && ccfg == 0 && mc && P.total > kWave && P.total % kWave <= kWave / 4)
                          ? P.total % kWave
                          : 0;
     if (tail > 0) {
@@ -634,7 +640,7 @@ Triple triple(const float* coeffs, int it) {
 // |B~| <= max |q| over [0, x], q(x) = a + b x + c x^2, and the next x is the
 // largest x q(x)^2.  The call qualifies while A and T stay below 8 (32768 as
 // stored, half of fp16's largest) and B~ below 32 (32768).
-bool half_ok(int iters, const float* coeffs, int precond) {
+bool half_ok(int iters, const float* coeffs, int precond, double top_b = 32.0) {
   if (precond == TM_PRECOND_NONE) return false;
   double x = 1.02;   // the scale's own rounding
   for (int it = 0; it < iters; ++it) {
@@ -643,7 +649,7 @@ bool half_ok(int iters, const float* coeffs, int precond) {
     auto q = [&](double v) { return a + b * v + c * v * v; };
     double top = std::max(std::fabs(a), std::fabs(q(x)));
     if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < x) top = std::max(top, std::fabs(q(-b / (2 * c))));
-    if (!(x <= 8.0 && top <= 32.0 && x * top <= 8.0)) return false;
+    if (!(x <= 8.0 && top <= top_b && x * top <= 8.0)) return false;
     double nx = 0.0;
     constexpr int S = 128;
     for (int i = 1; i <= S; ++i) {
@@ -677,12 +683,18 @@ bool pair_rule(const Item& it) {
   return it.k > 32 && 4 * uint64_t(it.N) >= 5 * uint64_t(it.k) && !small_eligible(it);
 }
 
+// fp32 matrices on fp16 planes: 4096 x 4096 12.65 -> 4.9 ms, 256 x 256 162 -> 105 us,
+// with a third of the error against 64 bits.  Short sides below 64 would be mostly padding
+// of the 64-wide tiles (a batch of many tiny matrices would need a workspace
+// several times its size).
+bool split_rule(const Item& it) { return it.k >= 64; }
+
 // The k x k products and update of iterations [it, it + n) of one class (1:
 // `pair`), n = 1 or 2, from A in kBufA; `scaled`: the update's factor times
 // diag(s).
-void block_steps(std::vector<Step>& out, bool pair, int it, int n, const float* coeffs, bool scaled,
+void block_steps(std::vector<Step>& out, bool pair, bool split, int it, int n, const float* coeffs, bool scaled,
                  int src, int dst) {
-  const float sa = pair ? tmk::kScaleA : 1.f, sb = pair ? tmk::kScaleB : 1.f;
+  const float sa = pair || split ? tmk::kScaleA : 1.f, sb = pair || split ? tmk::kScaleB : 1.f;
   auto product = [&](int l, int r, int m, int o, float al, float be, float ga, bool factor) {
     Step s{tmk::kKindPoly, 0u};
     s.l = l, s.r = r, s.m = m, s.out = o;
@@ -691,10 +703,10 @@ void block_steps(std::vector<Step>& out, bool pair, int it, int n, const float* 
                    : (!factor ? tmk::kSymHalf : (scaled ? tmk::kSymFactorScaled : tmk::kSymFactor));
     out.push_back(s);
   };
-  // B~ = b A + c A A + a I, times `f` (1 for an update's factor, else kScaleB)
+  // B~ = b A + c A A + a I, times `f` (1 for a bf16 update's factor, else kScaleB)
   auto poly = [&](int i, int o, bool factor) {
     const Triple t = triple(coeffs, i);
-    const float f = factor ? 1.f : sb;
+    const float f = factor && !split ? 1.f : sb;
     product(tmk::kBufA, tmk::kBufA, tmk::kBufA, o, t.c * (f / (sa * sa)), t.b * (f / sa), t.a * f, factor);
   };
   Step u{tmk::kKindUpdate, 0u};
@@ -746,8 +758,9 @@ tm_status run_steps(const Plan& pl, const std::vector<Step> (&seq)[2]) {
   return s;
 }
 
-// bf16: zero-padded tiled workspace, matrix-core kernels of tm_fast.hip.
-tm_status plan_bf16(const Plan& pl, int iters, const float* coeffs, int precond) {
+// bf16, and fp32 on fp16 planes (Plan::split): zero-padded tiled workspace,
+// matrix-core kernels of tm_fast.hip.
+tm_status plan_tiled(const Plan& pl, int iters, const float* coeffs, int precond) {
   const bool frob = precond == TM_PRECOND_FROBENIUS;
   const bool from_gram = precond == TM_PRECOND_AOL || precond == TM_PRECOND_SCHATTEN4;
   const bool scaled = from_gram || frob;
@@ -759,7 +772,8 @@ tm_status plan_bf16(const Plan& pl, int iters, const float* coeffs, int precond)
                       std::all_of(pl.items->begin(), pl.items->end(),
                                   [&](const Item& it) { return it.kp <= uint32_t(16 * part); });
   tm_status s = TM_OK;
-  if (iters > 0 || from_gram)
+  if (pl.split) s = launch(pl, tmk::kKindLoadIn, tmk::kCfgRowMax, 0, 0, 0.f, 0.f, 0.f, 0u, 0);
+  if (s == TM_OK && (iters > 0 || from_gram))
     s = launch(pl, tmk::kKindLoadIn, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0, kCoverCopied);
   if (s != TM_OK) return s;
   // the first Gram, of every matrix: A0 in fp32 where it is rescaled, then A1
@@ -802,7 +816,7 @@ tm_status plan_bf16(const Plan& pl, int iters, const float* coeffs, int precond)
         g.src = src;
         seq[cls].push_back(g);
       }
-      block_steps(seq[cls], cls == 1, it, n, coeffs, it == 0 && scaled, src, dst);
+      block_steps(seq[cls], cls == 1, pl.split, it, n, coeffs, it == 0 && scaled, src, dst);
       src = dst;
       it += n;
     }
@@ -896,47 +910,59 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) {
       return double(x.k) * x.k * x.N * x.count > double(y.k) * y.k * y.N * y.count;
     });
-  int tcfg = 0;
-  if (esz == 2) {
-    tcfg = choose_tile_cfg(items);
-    const bool half = iters >= 2 && half_ok(iters, coeffs, precond);
-    for (Item& it : items) {
-      tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(tcfg)), &it.kp, &it.Np);
-      // A wide matrix that needs no padding is read in place by the first
-      // update; a single update would read and write the caller's buffer in
-      // the same launch, so it keeps the copy.
-      it.pair = half && pair_rule(it);
-      const int updates = it.pair ? (iters + 1) / 2 : iters;
-      it.direct = !it.tall && it.kp == it.k && it.Np == it.N && updates != 1 &&
-                  (reinterpret_cast<uintptr_t>(it.x) & 15u) == 0u;
-    }
-  } else {
-    for (Item& it : items) tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
-  }
-  Plan pl;
-  pl.items = &items;
-  pl.esz = esz;
-  pl.st = st;
-  pl.tcfg = tcfg;
+  // parts of the call that run one after the other: bf16 is one, fp32 the
+  // matrices on fp16 planes and the others
+  std::vector<Item> part[2];
+  Plan pl[2];
   uint64_t total = 0;
-  for (const Item& it : items) {
-    pl.ws_off.push_back(total);
-    total += item_ws(it, esz);
+  const bool half = half_ok(iters, coeffs, precond);
+  const bool planes = esz == 4 && iters > 0 && half_ok(iters, coeffs, precond, 16.0);
+  for (const Item& it : items) part[esz == 2 || (planes && split_rule(it)) ? 0 : 1].push_back(it);
+  for (int p = 0; p < 2; ++p) {
+    if (part[p].empty()) continue;
+    pl[p].items = &part[p];
+    pl[p].esz = esz;
+    pl[p].st = st;
+    pl[p].split = p == 0 && esz == 4;
+    if (p == 0) {
+      pl[p].tcfg = choose_tile_cfg(part[p]);
+      for (Item& it : part[p]) {
+        tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);
+        it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
+        const int updates = it.pair ? (iters + 1) / 2 : iters;
+        // A wide matrix that needs no padding is read in place by the first
+        // update; a single update would read and write the caller's buffer in
+        // the same launch, so it keeps the copy.
+        it.direct = esz == 2 && !it.tall && it.kp == it.k && it.Np == it.N && updates != 1 &&
+                    (reinterpret_cast<uintptr_t>(it.x) & 15u) == 0u;
+      }
+    } else {
+      for (Item& it : part[p]) tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
+    }
+    for (const Item& it : part[p]) {
+      pl[p].ws_off.push_back(total);
+      total += item_ws(it, esz);
+    }
   }
   if (total >= (uint64_t(1) << 40))   // entries hold offsets in 256-byte units
     return fail(TM_ERR_UNSUPPORTED, "workspace of more than 1 TB");
+  char* ws = ext_ws;
   if (ext_ws != nullptr) {
     if (total > ext_bytes)
       return fail(TM_ERR_UNSUPPORTED, "the call needs " + std::to_string(total) +
                                           " bytes of scratch; the static scratch holds " +
                                           std::to_string(ext_bytes));
-    pl.ws = ext_ws;
-    pl.timed = false;
   } else {
-    s = get_workspace(dev, st, size_t(total), &pl.ws);
+    s = get_workspace(dev, st, size_t(total), &ws);
     if (s != TM_OK) return s;
   }
-  return esz == 2 ? plan_bf16(pl, iters, coeffs, precond) : plan_f32(pl, iters, coeffs, precond);
+  for (int p = 0; p < 2 && s == TM_OK; ++p) {
+    if (part[p].empty()) continue;
+    pl[p].ws = ws;
+    pl[p].timed = ext_ws == nullptr;
+    s = p == 0 ? plan_tiled(pl[p], iters, coeffs, precond) : plan_f32(pl[p], iters, coeffs, precond);
+  }
+  return s;
 }
 
 tm_status run(std::vector<Item>& items, int esz, int iters, const float* coeffs, int precond,
@@ -1194,12 +1220,20 @@ uint64_t tm_workspace_bytes(const int64_t* m, const int64_t* n, int64_t count, i
     if (m[g] < 1 || n[g] < 1 || m[g] > TM_MAX_DIM || n[g] > TM_MAX_DIM) return 0;
     items.push_back(make_item(nullptr, m[g], n[g], 1));
   }
-  if (items.empty()) return 0;
-  const int tcfg = dtype_bytes == 2 ? choose_tile_cfg(items) : 0;
+  // fp32: as if the coefficients allow the fp16 planes (the default ones do)
+  std::vector<Item> tiled;
   uint64_t total = 0;
   for (Item& it : items) {
-    if (dtype_bytes == 2) tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(tcfg)), &it.kp, &it.Np);
-    else tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
+    if (dtype_bytes == 2 || split_rule(it)) {
+      tiled.push_back(it);
+    } else {
+      tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
+      total += item_ws(it, dtype_bytes);
+    }
+  }
+  const int tcfg = tiled.empty() ? 0 : choose_tile_cfg(tiled);
+  for (Item& it : tiled) {
+    tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(tcfg)), &it.kp, &it.Np);
     total += item_ws(it, dtype_bytes);
   }
   return total;

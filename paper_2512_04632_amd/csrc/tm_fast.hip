@@ -1,4 +1,5 @@
-// bf16 matrix-core path of the Turbo-Muon orthogonalizer for gfx950 (MI355X).
+// bf16 matrix-core path of the Turbo-Muon orthogonalizer for gfx950 (MI355X),
+// and, compiled a second time, the fp32 path on fp16 planes.
 //
 // Every matrix is processed in a zero-padded workspace layout whose dims are
 // multiples of the square tile T (256, 128 or 64), so every tile is full: the
@@ -47,8 +48,47 @@
 
 #include "tm_internal.h"
 
+// Compiled twice: for bf16 storage, and (TM_SPLIT) for fp32 storage with every
+// matrix held as two fp16 planes.
+#ifndef TM_SPLIT
+#define TM_SPLIT 0
+#endif
+#if TM_SPLIT
+#define TM_FAST_NS split
+#else
+#define TM_FAST_NS fast
+#endif
+
 namespace tmk {
-namespace fast {
+namespace TM_FAST_NS {
+
+// fp32 storage on the fp16 matrix cores.  A value x scaled by a power of two is
+// hi + lo / 2048 with hi = fp16(x) and lo = fp16(2048 (x - hi)): 22 to 23 bits
+// as long as hi is a normal number (x above 2^-14).  A product A B is
+// (Ah Bl + Al Bh) / 2048 + Ah Bh in one fp32 accumulator: the K loop runs over
+// three segments with other planes, and the accumulators are scaled between
+// the second and the third (Al Bl, 2^-24 of the product, is left out).  Three
+// fp16 products run at about 1150 / 3 TFLOP/s against 87 to 115 of the fp32
+// matrix instructions here, and a K loop of 32-wide fp16 instructions rounds
+// its partial sums fewer times than one of 2-wide fp32 instructions.
+constexpr bool kSplit = TM_SPLIT != 0;
+constexpr uint32_t kEsz = kSplit ? 4 : 2;   // bytes per element of the workspace matrices
+constexpr int kSegs = kSplit ? 3 : 1;       // K segments of a product
+
+// Stage kt of a product whose K is nk / kSegs stages long: stage k within its
+// segment, and whether the a and b operands come from their lo planes (the
+// small products first).
+struct Seg {
+  int k;
+  bool alo, blo;
+};
+constexpr float kLoScale = 2048.f;
+__device__ inline Seg seg_of(int kt, int nk) {
+  if constexpr (!kSplit) return Seg{kt, false, false};
+  const int n = nk / kSegs;
+  const int s = (kt >= n ? 1 : 0) + (kt >= 2 * n ? 1 : 0);
+  return Seg{kt - s * n, s == 1, s == 0};
+}
 
 // K elements per ring stage of the 8-wave (256) tile: rows of 128 bytes.
 constexpr int kPingPongBK = 64;
@@ -396,6 +436,19 @@ __device__ inline void mma(AccT<T>& acc, const Frags<T>& fr) {
     }
 }
 
+// Before stage kt of a split product: the small products are summed.
+template <int T>
+__device__ inline void join_segments(AccT<T>& acc, int kt, int nk) {
+  if constexpr (kSplit) {
+    if (kt == nk / kSegs * 2) {
+#pragma unroll
+      for (int fm = 0; fm < Tile<T>::FM; ++fm)
+#pragma unroll
+        for (int fn = 0; fn < Tile<T>::FN; ++fn) acc[fm][fn] = acc[fm][fn] * (1.f / kLoScale);
+    }
+  }
+}
+
 // Runs slice(kt, s, cur, nxt) over every 32-wide slice s of every stage kt in
 // increasing K order; cur holds the slice's operands, nxt receives the next
 // one's.  With an even number of slices per stage the two operand buffers
@@ -433,8 +486,8 @@ __device__ inline void for_each_slice(int nk, Fr& f0, Fr& f1, Slice slice) {
 // that stalls every wave.  Slices are consumed in increasing order whatever BK
 // is, so every output element accumulates the same products in the same order.
 template <int T, bool RM, bool SWAP, int BK, bool H>
-__device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
-                                const uint16_t* b, int64_t ldb, int K) {
+__device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda, int64_t alo,
+                                const uint16_t* b, int64_t ldb, int64_t blo, int K) {
   using R = Ring<T, BK>;
   constexpr int PS = R::PER_STAGE, NS = BK / 32, NST = R::NSTAGE, DO = R::DMA_OP;
   constexpr int PPS = PS / NS;
@@ -444,15 +497,17 @@ __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int
   zero_acc<T>(acc);
 
   const uint32_t lds0 = lds_addr(smem);
-  const int nk = K / BK;
+  const int nk = kSegs * (K / BK);
   auto stage_lds = [&](int kt) { return lds0 + uint32_t((kt % NST) * R::STAGE); };
   // DMA instruction i (0 .. PS - 1) of stage kt: operand a first, then b
   auto dma_one = [&](int kt, int i) {
+    const Seg g = seg_of(kt, nk);
     if (i < DO) {
-      dma_kc<T, BK>(a, lda, kt * BK, stage_lds(kt), i);
+      dma_kc<T, BK>(g.alo ? a + alo : a, lda, g.k * BK, stage_lds(kt), i);
     } else {
-      if constexpr (RM) dma_rm<T, BK>(b, ldb, kt * BK, stage_lds(kt) + R::A_BYTES, i - DO);
-      else dma_kc<T, BK>(b, ldb, kt * BK, stage_lds(kt) + R::A_BYTES, i - DO);
+      const uint16_t* bp = g.blo ? b + blo : b;
+      if constexpr (RM) dma_rm<T, BK>(bp, ldb, g.k * BK, stage_lds(kt) + R::A_BYTES, i - DO);
+      else dma_kc<T, BK>(bp, ldb, g.k * BK, stage_lds(kt) + R::A_BYTES, i - DO);
     }
   };
   auto stage_ptr = [&](int kt) { return smem + (kt % NST) * R::STAGE; };
@@ -468,6 +523,7 @@ __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int
     const char* st = stage_ptr(kt);
     const int nx = kt + NST - 1;   // stage refilled during this one
     const bool fill = nx < nk;
+    if (s == 0) join_segments<T>(acc, kt, nk);
     if (s + 1 < NS) {
       load_frags<T, RM, BK>(nxt, st, st + R::A_BYTES, s + 1, wm, wn);
       if (fill)
@@ -506,8 +562,8 @@ __device__ inline void mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int
 // other loops.  The producer waves return afterwards; a barrier then waits
 // only for the waves still running.
 template <int T, bool SWAP, int BK, bool H>
-__device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
-                                   const uint16_t* b, int64_t ldb, int K) {
+__device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda, int64_t alo,
+                                   const uint16_t* b, int64_t ldb, int64_t blo, int K) {
   using R = Ring<T, BK>;
   constexpr int NW = Tile<T>::NW, NP = Tile<T>::NP, NS = BK / 32, NST = R::NSTAGE;
   constexpr int DOP = T * BK / 512 / NP;     // 1 KB DMAs per producer and operand stage
@@ -516,16 +572,18 @@ __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, 
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const bool prod = wave >= NW;
   const uint32_t lds0 = lds_addr(smem);
-  const int nk = K / BK;
+  const int nk = kSegs * (K / BK);
   auto stage_ptr = [&](int kt) { return smem + (kt % NST) * R::STAGE; };
   if (prod) {
     const int pw = wave - NW;
     auto issue = [&](int kt) {
       const uint32_t st = lds0 + uint32_t((kt % NST) * R::STAGE);
+      const Seg g = seg_of(kt, nk);
+      const uint16_t *ap = g.alo ? a + alo : a, *bp = g.blo ? b + blo : b;
 #pragma unroll
-      for (int q = 0; q < DOP; ++q) dma_kc_w<T, BK, NP>(a, lda, kt * BK, st, q, pw);
+      for (int q = 0; q < DOP; ++q) dma_kc_w<T, BK, NP>(ap, lda, g.k * BK, st, q, pw);
 #pragma unroll
-      for (int q = 0; q < DOP; ++q) dma_kc_w<T, BK, NP>(b, ldb, kt * BK, st + R::A_BYTES, q, pw);
+      for (int q = 0; q < DOP; ++q) dma_kc_w<T, BK, NP>(bp, ldb, g.k * BK, st + R::A_BYTES, q, pw);
     };
     for (int s = 0; s + 1 < NST && s < nk; ++s) issue(s);
     dma_wait_upto<PSP, NST - 2>(min(nk - 1, NST - 2));
@@ -545,6 +603,7 @@ __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, 
   load_frags<T, false, BK>(f0, stage_ptr(0), stage_ptr(0) + R::A_BYTES, 0, wm, wn);
   for_each_slice<NS>(nk, f0, f1, [&](int kt, int s, Frags<T>& cur, Frags<T>& nxt) {
     const char* st = stage_ptr(kt);
+    if (s == 0) join_segments<T>(acc, kt, nk);
     if (s + 1 < NS) {
       load_frags<T, false, BK>(nxt, st, st + R::A_BYTES, s + 1, wm, wn);
       mma<T, SWAP, H>(acc, cur);
@@ -587,8 +646,8 @@ __device__ inline bool mainloop_pc(AccT<T>& acc, char* smem, const uint16_t* a, 
 // a(j + 1), leaving a(j + 2) in flight: the barrier that opens group 0's
 // MEM(j + 1) comes after both.
 template <int T, bool RM, bool SWAP, int BK, bool H>
-__device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
-                                   const uint16_t* b, int64_t ldb, int K) {
+__device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda, int64_t alo,
+                                   const uint16_t* b, int64_t ldb, int64_t blo, int K) {
   static_assert(Tile<T>::NW == 8, "ping-pong needs two waves per SIMD");
   static_assert(BK == 64, "two 32-wide slices per stage");
   using R = Ring<T, BK>;
@@ -602,19 +661,23 @@ __device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, 
   zero_acc<T>(acc);
 
   const uint32_t lds0 = lds_addr(smem);
-  const int nk = K / BK;
+  const int nk = kSegs * (K / BK);
   auto slot_lds = [&](int i) { return lds0 + uint32_t((i % SLOTS) * R::A_BYTES); };
   auto slot_ptr = [&](int i) { return smem + (i % SLOTS) * R::A_BYTES; };
   // instructions q0 .. q1 - 1 of this wave's share of operand stage a(kt) / b(kt)
   auto issue_a = [&](int kt, int q0, int q1) {
+    const Seg g = seg_of(kt, nk);
+    const uint16_t* ap = g.alo ? a + alo : a;
 #pragma unroll
-    for (int q = q0; q < q1; ++q) dma_kc_w<T, BK, 4>(a, lda, kt * BK, slot_lds(2 * kt), q, w4);
+    for (int q = q0; q < q1; ++q) dma_kc_w<T, BK, 4>(ap, lda, g.k * BK, slot_lds(2 * kt), q, w4);
   };
   auto issue_b = [&](int kt, int q0, int q1) {
+    const Seg g = seg_of(kt, nk);
+    const uint16_t* bp = g.blo ? b + blo : b;
 #pragma unroll
     for (int q = q0; q < q1; ++q) {
-      if constexpr (RM) dma_rm_w<T, BK, 4>(b, ldb, kt * BK, slot_lds(2 * kt + 1), q, w4);
-      else dma_kc_w<T, BK, 4>(b, ldb, kt * BK, slot_lds(2 * kt + 1), q, w4);
+      if constexpr (RM) dma_rm_w<T, BK, 4>(bp, ldb, g.k * BK, slot_lds(2 * kt + 1), q, w4);
+      else dma_kc_w<T, BK, 4>(bp, ldb, g.k * BK, slot_lds(2 * kt + 1), q, w4);
     }
   };
 
@@ -652,6 +715,7 @@ __device__ inline void mainloop_pp(AccT<T>& acc, char* smem, const uint16_t* a, 
     }
     barrier_pinned();
     // COMP
+    join_segments<T>(acc, j, nk);
     mma<T, SWAP, H>(acc, f0);
     mma<T, SWAP, H>(acc, f1);
     if (!g1) dma_wait<0>();
@@ -671,20 +735,21 @@ __device__ inline const uint16_t* uniform(const uint16_t* p) {
   return reinterpret_cast<const uint16_t*>((uint64_t(hi) << 32) | lo);
 }
 
-// Returns false in the producer waves, which then leave the kernel.
+// alo, blo: elements from an operand's hi to its lo plane (split).  Returns
+// false in the producer waves, which then leave the kernel.
 template <int T, bool RM, bool SWAP, int BK, bool H = false>
-__device__ inline bool run_mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda,
-                                    const uint16_t* b, int64_t ldb, int K) {
+__device__ inline bool run_mainloop(AccT<T>& acc, char* smem, const uint16_t* a, int64_t lda, int64_t alo,
+                                    const uint16_t* b, int64_t ldb, int64_t blo, int K) {
   a = uniform(a);
   b = uniform(b);
   if constexpr (Tile<T>::NW == 8) {
-    mainloop_pp<T, RM, SWAP, BK, H>(acc, smem, a, lda, b, ldb, K);
+    mainloop_pp<T, RM, SWAP, BK, H>(acc, smem, a, lda, alo, b, ldb, blo, K);
     return true;
   } else if constexpr (RM) {   // the update's smaller tiles: compute waves issue the DMA
-    mainloop<T, RM, SWAP, BK, H>(acc, smem, a, lda, b, ldb, K);
+    mainloop<T, RM, SWAP, BK, H>(acc, smem, a, lda, alo, b, ldb, blo, K);
     return true;
   } else {
-    return mainloop_pc<T, SWAP, BK, H>(acc, smem, a, lda, b, ldb, K);
+    return mainloop_pc<T, SWAP, BK, H>(acc, smem, a, lda, alo, b, ldb, blo, K);
   }
 }
 
@@ -782,12 +847,14 @@ __device__ inline bool locate_by_matrix(const Phase& P, int p, Loc& L) {
 }
 
 __device__ inline char* ws_of(const Phase& P, const Entry& E, int mat) {
-  return P.ws + (uint64_t(E.ws256) << 8) + uint64_t(mat) * ws_layout(E.kp, E.Np, 2).total;
+  return P.ws + (uint64_t(E.ws256) << 8) + uint64_t(mat) * ws_layout(E.kp, E.Np, kEsz).total;
 }
 
 __device__ inline uint16_t* user_of(const Phase& P, const Entry& E, int mat) {
-  char* x = (E.flags & kPtrTab) ? P.xp[E.xbase + mat] : E.x + uint64_t(mat) * E.k * E.N * 2u;
-  return reinterpret_cast<uint16_t*>(x);
+  char* x = (E.flags & kPtrTab) ? P.xp[E.xbase + mat] : E.x + uint64_t(mat) * E.k * E.N * kEsz;
+  // device memory: said here, since the entry's scalar copy hides it (accesses
+  // would go through the flat path, one at a time)
+  return (uint16_t*)(__attribute__((address_space(1))) uint16_t*)reinterpret_cast<uint64_t>(x);
 }
 
 // Y buffer of a slot (kp x Np, ld ldy): the first slot is W1 (or, for a
@@ -796,7 +863,7 @@ __device__ inline uint16_t* user_of(const Phase& P, const Entry& E, int mat) {
 // update).
 __device__ inline uint16_t* wbuf(const Phase& P, const Entry& E, int mat, int slot) {
   if (slot == kSlotFirst && (E.flags & kDirect)) return user_of(P, E, mat);
-  const WsLayout L = ws_layout(E.kp, E.Np, 2);
+  const WsLayout L = ws_layout(E.kp, E.Np, kEsz);
   const bool w1 = slot == kSlotFirst || slot == kSlotAlt2;
   return reinterpret_cast<uint16_t*>(ws_of(P, E, mat) + (w1 ? L.w1 : L.w2));
 }
@@ -1106,8 +1173,8 @@ __device__ __forceinline__ void epilogue_sym_scaled(const AccT<T>& acc, char* st
 
 // fp32 store of an upper tile straight from the registers (first Gram only;
 // k_apply_s reads the upper tiles and writes both halves of A1).
-template <int T>
-__device__ inline void store_sym_f32(const AccT<T>& acc, float* D, int64_t ld, int I, int J) {
+template <int T, class Fv>
+__device__ __forceinline__ void store_sym_f32(float* D, int64_t ld, int I, int J, Fv block) {
   const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
 #pragma unroll
   for (int fm = 0; fm < Tile<T>::FM; ++fm)
@@ -1115,9 +1182,65 @@ __device__ inline void store_sym_f32(const AccT<T>& acc, float* D, int64_t ld, i
     for (int fn = 0; fn < Tile<T>::FN; ++fn) {
       const int j = J * T + acc_col<T>(wn, fn);
       const int ib = I * T + acc_row<T>(wm, fm);
+      const f32x4_t x = block(fm, fn);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) D[int64_t(ib + u) * ld + j] = acc[fm][fn][u];
+      for (int u = 0; u < 4; ++u) D[int64_t(ib + u) * ld + j] = x[u];
     }
+}
+
+// ---------------------------------------------------------------- split epilogues
+// hi or lo plane (p = 0, 1) of a scaled value.
+__device__ inline uint16_t plane_of(float x, int p) {
+  const uint16_t h = f2h(x);
+  return p == 0 ? h : f2h((x - h2f(h)) * kLoScale);
+}
+
+// An accumulator block as a new value: keeps what is computed from it inside
+// the pass over the planes (hoisted out, the 256 tile's would spill).
+__device__ inline f32x4_t fresh(f32x4_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Symmetric product: f(i_local, j_local, acc block, v) fills the values of 4
+// consecutive rows i of column j; the tile goes out plane by plane as rows of
+// tile (J, I) (element (j, i)) and, off the diagonal, transposed as tile
+// (I, J).  With two values per element (scaled: the mirror's and the tile's
+// differ) f is asked for each, which = 0, 1.
+template <int T, bool TWO, class Fv>
+__device__ __forceinline__ void epilogue_split(const AccT<T>& acc, char* st, uint16_t* D, int64_t lo,
+                                               int64_t ld, int I, int J, Fv f) {
+  const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
+#pragma unroll 1
+  for (int q = 0; q < (TWO && I != J ? 4 : 2); ++q) {
+    const int p = q & 1, which = q >> 1;
+    if (q > 0) __syncthreads();
+#pragma unroll
+    for (int fm = 0; fm < Tile<T>::FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < Tile<T>::FN; ++fn) {
+        const int c = acc_col<T>(wn, fn);
+        const int r0 = acc_row<T>(wm, fm);
+        float v[4];
+        f(r0, c, fresh(acc[fm][fn]), which, v);
+        const uint32_t w0 = plane_of(v[0], p) | uint32_t(plane_of(v[1], p)) << 16;
+        const uint32_t w1 = plane_of(v[2], p) | uint32_t(plane_of(v[3], p)) << 16;
+        *reinterpret_cast<uint2*>(st + c * Stage<T>::RS + r0 * 2) = make_uint2(w0, w1);
+        __builtin_amdgcn_sched_barrier(0);   // keeps the loads of the next block here
+      }
+    __syncthreads();
+    uint16_t* Dp = D + p * lo;
+    if (which == 0) store_rows<T>(st, Dp, ld, int64_t(J) * T, int64_t(I) * T);
+    if (I != J && (!TWO || which == 1)) store_cols<T>(st, Dp, ld, int64_t(I) * T, int64_t(J) * T);
+  }
+}
+
+// Row scales r_i of the split input: X_ij = r_i (plane value), kept in W2 until
+// the first update writes it, after the partial row maxima.
+__device__ inline uint32_t max_chunks(uint32_t N) { return cdiv(N, kMaxCols); }
+__device__ inline float* row_max(char* w, const WsLayout& L) { return reinterpret_cast<float*>(w + L.w2); }
+__device__ inline float* row_scale(char* w, const WsLayout& L, const Entry& E) {
+  return row_max(w, L) + uint64_t(max_chunks(E.N)) * E.kp;
 }
 
 // ---------------------------------------------------------------- kernels
@@ -1132,21 +1255,43 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
   const int kp = int(E.kp), Np = int(E.Np);
   const uint16_t* Y = wbuf(P, E, L.mat, Ops(E.flags).src());
   char* w = ws_of(P, E, L.mat);
-  const WsLayout WL = ws_layout(E.kp, E.Np, 2);
+  const WsLayout WL = ws_layout(E.kp, E.Np, kEsz);
   const int64_t ldy = WL.ldy;
   AccT<T> acc;
-  if (!run_mainloop<T, false, false, BK>(acc, smem, Y + int64_t(I) * T * ldy, ldy, Y + int64_t(J) * T * ldy, ldy, Np)) return;
+  const int64_t ylo = int64_t(kp) * ldy;
+  if (!run_mainloop<T, false, false, BK, kSplit>(acc, smem, Y + int64_t(I) * T * ldy, ldy, ylo,
+                                                 Y + int64_t(J) * T * ldy, ldy, ylo, Np))
+    return;
 
-  if (P.flags & kA32) {
-    store_sym_f32<T>(acc, reinterpret_cast<float*>(w + WL.a32), kp, I, J);
-  } else {
+  if ((P.flags & kA32) == 0u) {
     uint16_t* A = reinterpret_cast<uint16_t*>(w + WL.a);
-    if (E.flags & kPair)
+    if constexpr (kSplit)
+      epilogue_split<T, false>(acc, smem, A, int64_t(kp) * kp, WL.ldg, I, J,
+                               [](int, int, const f32x4_t& x, int, float (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+                                 for (int u = 0; u < 4; ++u) v[u] = x[u] * (kScaleA / (kScaleY * kScaleY));
+                               });
+    else if (E.flags & kPair)
       epilogue_sym<T>(acc, smem, A, WL.ldg, I, J, 0,
                       [](int, int, float x, uint16_t) { return f2h(x * kScaleA); });
     else
       epilogue_sym<T>(acc, smem, A, WL.ldg, I, J, 0, [](int, int, float x, uint16_t) { return f2bf(x); });
+    return;
   }
+  // A0's block (fm, fn); split: X0's planes are scaled row by row
+  const float* xs = row_scale(w, WL, E);
+  auto a0 = [&](int fm, int fn) __attribute__((always_inline)) {
+    f32x4_t x = acc[fm][fn];
+    if constexpr (kSplit) {
+      x = fresh(x);
+      const float4 ri = *reinterpret_cast<const float4*>(
+          xs + I * T + acc_row<T>(wave_m(Tile<T>::WGN), fm));
+      const float rj = xs[J * T + acc_col<T>(wave_n(Tile<T>::WGN), fn)];
+      x = f32x4_t{x[0] * ri.x * rj, x[1] * ri.y * rj, x[2] * ri.z * rj, x[3] * ri.w * rj};
+    }
+    return x;
+  };
+  store_sym_f32<T>(reinterpret_cast<float*>(w + WL.a32), kp, I, J, a0);
 
   // The host never asks a 32 tile for row sums (their partials cover 64 columns).
   if (T >= kMinTile && (P.flags & kRowSum)) {
@@ -1173,18 +1318,18 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
     for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn) {
+        const f32x4_t e = a0(fm, fn);
         // row sums: lanes 16 g .. 16 g + 15 hold the 16 columns of rows
         // 4 g + v; butterfly over lane bits 0..3
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          float x = mag(acc[fm][fn][v]);
+          float x = mag(e[v]);
 #pragma unroll
           for (int off = 1; off <= 8; off <<= 1) x += __shfl_xor(x, off, 64);
           if ((lane & 15) == 0) rs[((wn * Tile<T>::TWN) / 16 + fn) * T + acc_row<T>(wm, fm) + v] = x;
         }
         // column sums: row bits 0, 1 are v's, bits 2, 3 the lane's bits 4, 5
-        const float y = (mag(acc[fm][fn][0]) + mag(acc[fm][fn][1])) +
-                        (mag(acc[fm][fn][2]) + mag(acc[fm][fn][3]));
+        const float y = (mag(e[0]) + mag(e[1])) + (mag(e[2]) + mag(e[3]));
         float col = y + __shfl_xor(y, 16, 64);
         col += __shfl_xor(col, 32, 64);
         if (lane < 16) cs[((wm * Tile<T>::TWM) / 16 + fm) * T + acc_col<T>(wn, fn)] = col;
@@ -1215,12 +1360,38 @@ __device__ __forceinline__ void sym_block(const Phase& P, const Entry& E, char* 
                                           int J) {
   const Ops op(E.flags);
   const int kp = int(E.kp);
-  const WsLayout WL = ws_layout(E.kp, E.Np, 2);
+  const WsLayout WL = ws_layout(E.kp, E.Np, kEsz);
   const int64_t ldg = WL.ldg;
   AccT<T> acc;
-  if (!run_mainloop<T, false, false, BK, H>(acc, smem, kbuf(w, WL, op.l()) + int64_t(I) * T * ldg, ldg,
-                                            kbuf(w, WL, op.r()) + int64_t(J) * T * ldg, ldg, kp))
+  const int64_t glo = int64_t(kp) * ldg;
+  if (!run_mainloop<T, false, false, BK, H>(acc, smem, kbuf(w, WL, op.l()) + int64_t(I) * T * ldg, ldg, glo,
+                                            kbuf(w, WL, op.r()) + int64_t(J) * T * ldg, ldg, glo, kp))
     return;
+  if constexpr (kSplit) {
+    __syncthreads();
+    const float al = P.c, be = P.b, ga = P.a;
+    const uint16_t* M = kbuf(w, WL, op.m()) + int64_t(J) * T * ldg + int64_t(I) * T;   // element (j, i)
+    const float* s = reinterpret_cast<const float*>(w + WL.s);
+    const float* rs = row_scale(w, WL, E);
+    const int diag = I == J;
+    auto val = [=](int i0, int j, const f32x4_t& x, int which, float (&v)[4]) __attribute__((always_inline)) {
+      const uint2 mh = *reinterpret_cast<const uint2*>(M + int64_t(j) * ldg + i0);
+      const uint2 ml = *reinterpret_cast<const uint2*>(M + glo + int64_t(j) * ldg + i0);
+      const uint32_t h[2] = {mh.x, mh.y}, l[2] = {ml.x, ml.y};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float m = __builtin_fmaf(h2f(uint16_t(l[u >> 1] >> (16 * (u & 1)))), 1.f / kLoScale,
+                                       h2f(uint16_t(h[u >> 1] >> (16 * (u & 1)))));
+        v[u] = __builtin_fmaf(be, m, al * x[u]) + ((diag && i0 + u == j) ? ga : 0.f);
+        if constexpr (MODE == kSymBf16Scaled) {   // column scale of X0's plane: s r kScaleY
+          const int q = which == 0 ? I * T + i0 + u : J * T + j;
+          v[u] *= s[q] * (rs[q] * kScaleY);
+        }
+      }
+    };
+    epilogue_split<T, MODE == kSymBf16Scaled>(acc, smem, kbuf(w, WL, op.out()), glo, ldg, I, J, val);
+    return;
+  }
   const int hasm = !H || op.m() != kNoBuf;
   if (hasm) load_rows<T>(smem, kbuf(w, WL, op.m()), ldg, int64_t(J) * T, int64_t(I) * T);
   __syncthreads();
@@ -1254,7 +1425,7 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_sym_fast(const Phase P) {
     if (L.E.flags & kPair) sym_block<T, BK, MODE, true>(P, L.E, smem, w, I, J);
     else sym_block<T, BK, MODE, false>(P, L.E, smem, w, I, J);
   } else {
-    sym_block<T, BK, MODE, (MODE >= kSymHalf)>(P, L.E, smem, w, I, J);
+    sym_block<T, BK, MODE, kSplit || (MODE >= kSymHalf)>(P, L.E, smem, w, I, J);
   }
 }
 
@@ -1291,20 +1462,70 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
   const int Lb = F * (rem / gsz) + sub % F;
 
   char* w = ws_of(P, E, L.mat);
-  const WsLayout WL = ws_layout(E.kp, E.Np, 2);
+  const WsLayout WL = ws_layout(E.kp, E.Np, kEsz);
   const Ops op(E.flags);
   const int dst = op.dst();
   const uint16_t* B = kbuf(w, WL, op.fac());
   const uint16_t* Y = wbuf(P, E, L.mat, op.src());
   const int64_t ldg = WL.ldg, ldy = WL.ldy;
   AccT<T> acc;
-  run_mainloop<T, true, true, BK>(acc, smem, B + int64_t(I) * T * ldg, ldg, Y + int64_t(Lb) * T, ldy, kp);
+  run_mainloop<T, true, true, BK, kSplit>(acc, smem, B + int64_t(I) * T * ldg, ldg, int64_t(kp) * ldg,
+                                          Y + int64_t(Lb) * T, ldy, int64_t(kp) * ldy, kp);
 
   // acc[fm][fn] element u: output row i = wm*TWM + fm*16 + lane%16, column
   // l0 + u with l0 = 16 (fn WGN + wn) + 4(lane/16) (the waves' column blocks
   // interleave, as the operand reads of the row-major Y stage assign them)
   const int lane = threadIdx.x & 63;
   const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
+  if constexpr (kSplit) {
+    if (dst != kSlotFinal) {
+      uint16_t* D = wbuf(P, E, L.mat, dst);
+#pragma unroll 1
+      for (int p = 0; p < 2; ++p) {
+        if (p > 0) __syncthreads();
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+          for (int fn = 0; fn < FN; ++fn) {
+            const int i = wm * Tile<T>::TWM + fm * 16 + (lane & 15);
+            const int l0 = 16 * (fn * Tile<T>::WGN + wn) + 4 * (lane >> 4);
+            const f32x4_t x = fresh(acc[fm][fn]);
+            uint32_t o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = plane_of(x[u] * (1.f / kScaleB), p);
+            *reinterpret_cast<uint2*>(smem + i * Stage<T>::RS + l0 * 2) =
+                make_uint2(o[0] | o[1] << 16, o[2] | o[3] << 16);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        __syncthreads();
+        store_rows<T>(smem, D + p * int64_t(kp) * ldy, ldy, int64_t(I) * T, int64_t(Lb) * T);
+      }
+      return;
+    }
+    // the caller's fp32 matrix, straight from the registers: 64-byte row pieces
+    float* X = reinterpret_cast<float*>(user_of(P, E, L.mat));
+    const bool tall = (E.flags & kTall) != 0u;
+    const bool vec = (N % 4) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0u;
+    constexpr float f = 1.f / (kScaleB * kScaleY);
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) {
+        const int i = I * T + wm * Tile<T>::TWM + fm * 16 + (lane & 15);
+        const int l = Lb * T + 16 * (fn * Tile<T>::WGN + wn) + 4 * (lane >> 4);
+        if (i >= k) continue;
+        const f32x4_t v = acc[fm][fn] * f;
+        if (!tall && vec && l + 4 <= N) {
+          *reinterpret_cast<f32x4_t*>(X + int64_t(i) * N + l) = v;
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (l + u < N) X[tall ? int64_t(l + u) * k + i : int64_t(i) * N + l + u] = v[u];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    return;
+  }
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
@@ -1336,7 +1557,7 @@ __global__ __launch_bounds__(256) void k_load_in(const Phase P) {
   const Loc L = locate(P, blockIdx.x);
   const Entry& E = L.E;
   const int k = int(E.k), N = int(E.N);
-  const int64_t ldy = ws_layout(E.kp, E.Np, 2).ldy;
+  const int64_t ldy = ws_layout(E.kp, E.Np, kEsz).ldy;
   const int nI = int(E.kp) / kTransposeTile;
   const int ti = L.tile % nI, tl = L.tile / nI;
   const uint16_t* X = user_of(P, E, L.mat);
@@ -1391,6 +1612,137 @@ __global__ __launch_bounds__(256) void k_load_in(const Phase P) {
   }
 }
 
+// fp32 input: largest magnitude of each row of the wide view over kMaxCols
+// columns, one block per 64 rows x kMaxCols columns, so that the pass fills the
+// chip.  Bound by memory: every load of a thread is in flight before the first
+// maximum (a load outside the matrix reads its first element and counts as
+// zero, so that none sits behind a branch).
+__global__ __launch_bounds__(256) void k_row_max(const Phase P) {
+  __shared__ float red[4][64];
+  const Loc L = locate(P, blockIdx.x);
+  const Entry& E = L.E;
+  const int k = int(E.k), N = int(E.N);
+  const int nI = int(E.kp) / 64;
+  const int ti = L.tile % nI, ch = L.tile / nI;
+  const float* X = reinterpret_cast<const float*>(user_of(P, E, L.mat));
+  float* pm = row_max(ws_of(P, E, L.mat), ws_layout(E.kp, E.Np, kEsz)) + int64_t(ch) * E.kp + ti * 64;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l0 = ch * int(kMaxCols), l1 = min(N, l0 + int(kMaxCols));
+  float m[16], v[16];
+  if (E.flags & kTall) {   // a lane per row of the wide view = column of X
+    const int i = ti * 64 + lane;
+    float r = 0.f;
+#pragma unroll 1
+    for (int h = 0; h < int(kMaxCols) / 64; ++h) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int l = l0 + 64 * h + 4 * q + w;
+        v[q] = X[i < k && l < l1 ? int64_t(l) * k + i : 0];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        r = fmaxf(r, i < k && l0 + 64 * h + 4 * q + w < l1 ? fabsf(v[q]) : 0.f);
+    }
+    red[w][lane] = r;
+    __syncthreads();
+    if (w == 0) pm[lane] = fmaxf(fmaxf(red[0][lane], red[1][lane]), fmaxf(red[2][lane], red[3][lane]));
+  } else {                 // wave w: rows 16 w .. 16 w + 15, a lane per column
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m[q] = 0.f;
+#pragma unroll 2
+    for (int h = 0; h < int(kMaxCols) / 64; ++h) {
+      const int l = l0 + 64 * h + lane;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int i = ti * 64 + 16 * w + q;
+        v[q] = X[i < k && l < l1 ? int64_t(i) * N + l : 0];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        m[q] = fmaxf(m[q], ti * 64 + 16 * w + q < k && l < l1 ? fabsf(v[q]) : 0.f);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) m[q] = fmaxf(m[q], __shfl_xor(m[q], off, 64));
+    if (lane == 0) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) pm[16 * w + q] = m[q];
+    }
+  }
+}
+
+// W1 = the planes of X (wide) or X^T (tall), zero padded: row i scaled by
+// kScaleY 2^-e with 2^(e - 1) <= the row's largest magnitude < 2^e, so that
+// rows of any size keep their bits; r_i = 2^e / kScaleY is kept for the first
+// Gram and polynomial.  One block per 64 x 64 tile.
+__global__ __launch_bounds__(256) void k_load_split(const Phase P) {
+  __shared__ float tile[64][65];
+  __shared__ float up[64];
+  const Loc L = locate(P, blockIdx.x);
+  const Entry& E = L.E;
+  const int k = int(E.k), N = int(E.N);
+  char* w = ws_of(P, E, L.mat);
+  const WsLayout WL = ws_layout(E.kp, E.Np, kEsz);
+  const int64_t ldy = WL.ldy;
+  const int nI = int(E.kp) / 64;
+  const int ti = L.tile % nI, tl = L.tile / nI;
+  const float* X = reinterpret_cast<const float*>(user_of(P, E, L.mat));
+  const bool tall = (E.flags & kTall) != 0u;
+  const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
+  if (threadIdx.x < 64) {
+    const float* pm = row_max(w, WL) + ti * 64 + threadIdx.x;
+    const int nch = int(max_chunks(E.N));
+    float m = 0.f;
+#pragma unroll 4
+    for (int q = 0; q < nch; ++q) m = fmaxf(m, pm[int64_t(q) * E.kp]);
+    // exponent e, held in [-100, 128] so that both scales are normal numbers;
+    // an all-zero row keeps e = 0
+    const int e = m > 0.f ? min(max(int(__float_as_uint(m) >> 23) - 126, -100), 128) : 0;
+    up[threadIdx.x] = __uint_as_float(uint32_t(127 + 14 - e) << 23);
+    if (tl == 0) row_scale(w, WL, E)[ti * 64 + threadIdx.x] = __uint_as_float(uint32_t(127 - 14 + e) << 23);
+  }
+  // tile row r: X row ti 64 + r (wide) or tl 64 + r (tall), columns from the
+  // other tile index; all loads of a thread in flight, none behind a branch
+  const int ra = (tall ? tl : ti) * 64, ca = (tall ? ti : tl) * 64 + c;
+  const int nr = tall ? N : k, nc = tall ? k : N;
+  float v[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = ra + g + 4 * q;
+    v[q] = X[r < nr && ca < nc ? int64_t(r) * nc + ca : 0];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = g + 4 * q;
+    const float x = ra + r < nr && ca < nc ? v[q] : 0.f;
+    if (tall) tile[c][r] = x;
+    else tile[r][c] = x;
+  }
+  __syncthreads();
+  uint16_t* W = wbuf(P, E, L.mat, kSlotFirst);
+  const int64_t lo = int64_t(E.kp) * ldy;
+  const int c8 = threadIdx.x & 7, r0 = threadIdx.x >> 3;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = r0 + 32 * h;
+    uint32_t hi[4], lw[4];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float x = tile[r][c8 * 8 + u] * up[r];
+      const uint32_t a = plane_of(x, 0), b = plane_of(x, 1);
+      hi[u >> 1] = (u & 1) ? (hi[u >> 1] | a << 16) : a;
+      lw[u >> 1] = (u & 1) ? (lw[u >> 1] | b << 16) : b;
+    }
+    uint16_t* d = W + int64_t(ti * 64 + r) * ldy + tl * 64 + c8 * 8;
+    *reinterpret_cast<uint4*>(d) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    *reinterpret_cast<uint4*>(d + lo) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+  }
+}
+
 // First iteration after the scaling: A1 = s_i A0_ij s_j, rounded once (bf16, or
 // fp16 for a kPair entry).  The Gram
 // stored A0 (fp32) as its upper tiles only, which contain every upper 64 x 64
@@ -1407,7 +1759,7 @@ __global__ __launch_bounds__(256) void k_apply_s(const Phase P) {
   const Entry& E = L.E;
   const int kp = int(E.kp);
   char* w = ws_of(P, E, L.mat);
-  const WsLayout WL = ws_layout(E.kp, E.Np, 2);
+  const WsLayout WL = ws_layout(E.kp, E.Np, kEsz);
   float* s = reinterpret_cast<float*>(w + WL.s);
   const float* A0 = reinterpret_cast<const float*>(w + WL.a32);
   uint16_t* A = reinterpret_cast<uint16_t*>(w + WL.a);
@@ -1437,6 +1789,30 @@ __global__ __launch_bounds__(256) void k_apply_s(const Phase P) {
   const int i = I * 64 + r, j0 = J * 64 + c0;
   const float si = sv[r];
   const float* src = A0 + int64_t(i) * kp + j0;
+  if constexpr (kSplit) {   // both planes of the tile, then of its mirror
+    const int64_t lo = int64_t(kp) * WL.ldg;
+#pragma unroll 1
+    for (int p = 0; p < 2; ++p) {
+      uint16_t o[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) o[q] = plane_of(src[q] * (si * sv[64 + c0 + q]) * kScaleA, p);
+      uint16_t* dst = A + p * lo + int64_t(i) * WL.ldg + j0;
+      reinterpret_cast<uint4*>(dst)[0] = reinterpret_cast<const uint4*>(o)[0];
+      reinterpret_cast<uint4*>(dst)[1] = reinterpret_cast<const uint4*>(o)[1];
+      if (I == J) continue;   // uniform per block
+      if (p > 0) __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 16; ++e) tt[r][c0 + e] = o[e];
+      __syncthreads();
+      uint16_t m[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) m[e] = tt[c0 + e][r];
+      uint16_t* d2 = A + p * lo + int64_t(J * 64 + r) * WL.ldg + I * 64 + c0;
+      reinterpret_cast<uint4*>(d2)[0] = reinterpret_cast<const uint4*>(m)[0];
+      reinterpret_cast<uint4*>(d2)[1] = reinterpret_cast<const uint4*>(m)[1];
+    }
+    return;
+  }
   uint16_t o[16];
   auto round = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
@@ -1477,10 +1853,12 @@ static hipError_t launch_t(int kind, const Phase& P, hipStream_t st) {
       switch (P.symmode) {
         case kSymBf16: TM_LAUNCH((k_sym_fast<T, BK, kSymBf16>));
         case kSymBf16Scaled: TM_LAUNCH((k_sym_fast<T, BK, kSymBf16Scaled>));
+#if !TM_SPLIT
         case kSymHalf: TM_LAUNCH((k_sym_fast<T, BK, kSymHalf>));
         case kSymFactor: TM_LAUNCH((k_sym_fast<T, BK, kSymFactor>));
         case kSymFactorScaled: TM_LAUNCH((k_sym_fast<T, BK, kSymFactorScaled>));
         case kSymMixed: TM_LAUNCH((k_sym_fast<T, BK, kSymMixed>));
+#endif
       }
       break;
     case kKindUpdate:
@@ -1493,29 +1871,38 @@ static hipError_t launch_t(int kind, const Phase& P, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-}  // namespace fast
+}  // namespace TM_FAST_NS
 
+#if TM_SPLIT
+hipError_t launch_split_f32(int kind, int cfg, int step, const Phase& P, hipStream_t st) {
+#else
 hipError_t launch_fast_bf16(int kind, int cfg, int step, const Phase& P, hipStream_t st) {
+#endif
   if (P.total <= 0) return hipSuccess;
   if (kind == kKindLoadIn) {
-    hipLaunchKernelGGL(fast::k_load_in, dim3(P.total), dim3(256), 0, st, P);
+#if TM_SPLIT
+    if (cfg == kCfgRowMax) hipLaunchKernelGGL(TM_FAST_NS::k_row_max, dim3(P.total), dim3(256), 0, st, P);
+    else hipLaunchKernelGGL(TM_FAST_NS::k_load_split, dim3(P.total), dim3(256), 0, st, P);
+    return hipGetLastError();
+#endif
+    hipLaunchKernelGGL(TM_FAST_NS::k_load_in, dim3(P.total), dim3(256), 0, st, P);
     return hipGetLastError();
   }
   if (kind == kKindScaleA) {
-    hipLaunchKernelGGL(fast::k_apply_s, dim3(P.total), dim3(256), 0, st, P);
+    hipLaunchKernelGGL(TM_FAST_NS::k_apply_s, dim3(P.total), dim3(256), 0, st, P);
     return hipGetLastError();
   }
   switch (cfg_tile(cfg)) {
-    case 256: return fast::launch_t<256, fast::kPingPongBK>(kind, P, st);
+    case 256: return TM_FAST_NS::launch_t<256, TM_FAST_NS::kPingPongBK>(kind, P, st);
     case 128:
-      return step == 64 ? fast::launch_t<128, 64>(kind, P, st) : fast::launch_t<128, 32>(kind, P, st);
+      return step == 64 ? TM_FAST_NS::launch_t<128, 64>(kind, P, st) : TM_FAST_NS::launch_t<128, 32>(kind, P, st);
     case 64:
-      return step == 128 ? fast::launch_t<64, 128>(kind, P, st)
-             : step == 64 ? fast::launch_t<64, 64>(kind, P, st)
-                          : fast::launch_t<64, 32>(kind, P, st);
+      return step == 128 ? TM_FAST_NS::launch_t<64, 128>(kind, P, st)
+             : step == 64 ? TM_FAST_NS::launch_t<64, 64>(kind, P, st)
+                          : TM_FAST_NS::launch_t<64, 32>(kind, P, st);
     case 32:
       if (kind == kKindUpdate || (kind == kKindGram && (P.flags & kRowSum))) break;
-      return step == 128 ? fast::launch_t<32, 128>(kind, P, st) : fast::launch_t<32, 32>(kind, P, st);
+      return step == 128 ? TM_FAST_NS::launch_t<32, 128>(kind, P, st) : TM_FAST_NS::launch_t<32, 32>(kind, P, st);
   }
   return hipErrorInvalidValue;
 }

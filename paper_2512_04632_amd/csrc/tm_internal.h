@@ -75,6 +75,11 @@ constexpr uint32_t kPair = 8u;    // bf16: two iterations per update (Phase's se
 // off-diagonal entries of large Gram matrices stay normal.
 constexpr float kScaleA = 4096.f;
 constexpr float kScaleB = 1024.f;
+// fp32 path on fp16 planes: scale of Y (sigma_max < 2.83: below 46341).
+constexpr float kScaleY = 16384.f;
+// cfg of a load-in launch of that path that takes the rows' maxima.
+constexpr int kCfgRowMax = 1;
+constexpr uint32_t kMaxCols = 256;   // columns of one such maximum
 
 // The k x k buffers of a matrix: A, B and T, which shares the fp32 first
 // Gram's memory (dead once it has been rescaled).
@@ -226,7 +231,9 @@ TM_HD uint32_t blocks_per_matrix(int kind, int cfg, uint32_t k, uint32_t N, uint
   const uint32_t T = uint32_t(cfg_tile(cfg));
   switch (kind) {
     case kKindTransposeIn: return cdiv(k, kTransposeTile) * cdiv(N, kTransposeTile);
-    case kKindLoadIn: return cdiv(kp, kTransposeTile) * cdiv(Np, kTransposeTile);
+    case kKindLoadIn:
+      return cfg == kCfgRowMax ? cdiv(kp, kTransposeTile) * cdiv(N, kMaxCols)
+                               : cdiv(kp, kTransposeTile) * cdiv(Np, kTransposeTile);
     case kKindFrob: return uint32_t(kFrobBlocks);
     case kKindGram:
     case kKindPoly: return tri(cdiv(kp, T));

@@ -15,7 +15,9 @@
 //                    iteration 1 the rescaled X1 = diag(s) X0 is folded in
 //   k_apply_scale    iters = 0: X1 = diag(s) X0 in place
 //
-// These are the fp32 path's kernels; a bf16 call runs only the elementwise
+// These are the fp32 path's kernels for matrices of fewer than 64 rows, for
+// calls without a pre-conditioner and for coefficients beyond fp16's range (the
+// others run on fp16 planes, tm_fast.hip); a bf16 call runs only the elementwise
 // ones from here (Frobenius partials, AOL vector, iters = 0 rescale) and its
 // matrix-core phases in tm_fast.hip.
 //
@@ -128,7 +130,7 @@ __device__ inline char* ws_of(const Phase& P, const Entry& E, int mat) {
 template <typename T>
 __device__ inline T* user_of(const Phase& P, const Entry& E, int mat) {
   char* x = (E.flags & kPtrTab) ? P.xp[E.xbase + mat] : E.x + uint64_t(mat) * E.k * E.N * sizeof(T);
-  return reinterpret_cast<T*>(x);
+  return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uint64_t>(x);   // device memory, not flat
 }
 
 // Wide-view Y buffer of a slot (ld = N), see tm_internal.h.
