@@ -170,7 +170,7 @@ uint64_t item_ws(const Item& it, int esz) {
 
 // Generic (fp32) path: pick per phase the largest tile whose launch still
 // spans one wave of the chip's 256 compute units; otherwise the smallest.
-int choose_cfg(int kind, const std::vector<Item>& items) {
+int choose_cfg_f32(int kind, const std::vector<Item>& items) {
   for (int cfg = 0; cfg < tmk::kNumCfg - 1; ++cfg) {
     uint64_t tiles = 0;
     for (const Item& it : items)
@@ -180,52 +180,110 @@ int choose_cfg(int kind, const std::vector<Item>& items) {
   return tmk::kNumCfg - 1;
 }
 
-// bf16 path: the layout tile of the call (the Gram and polynomial may run
-// smaller tiles of it).  Take the largest tile whose zero padding adds at most
-// 30% to the call's products and whose update still has about two waves of
-// tiles for the 256 compute units; the 256 tile also needs update tiles with
-// a mean K of at least 512, below which its fixed costs per tile (pipeline
-// fill, the 128 KB epilogue) outweigh its faster main loop.
-int choose_tile_cfg(const std::vector<Item>& items) {
+// The items with neighbours of one shape joined: what the choice of a tile
+// looks at (a group of many matrices has few shapes; choosing for each launch
+// over every matrix would cost as much host time as a small call takes).
+std::vector<Item> shapes_of(const std::vector<Item>& items) {
+  std::vector<Item> out;
+  for (const Item& it : items) {
+    if (!out.empty() && out.back().k == it.k && out.back().N == it.N && out.back().kp == it.kp &&
+        out.back().Np == it.Np && out.back().pair == it.pair)
+      out.back().count += it.count;
+    else
+      out.push_back(it);
+  }
+  return out;
+}
+
+// Time of one matrix-core launch over `items` with a tile size, in
+// microseconds without the launch itself.  A tile costs its compute unit f + r K
+// (K elements of its contraction), and a launch at least its longest tile alone
+// on a unit, f1 + r1 K.  Measured:
+//   256: 13 + 0.024 K (one block per unit: pipeline fill and the 128 KB epilogue
+//        are not hidden), in waves of one block per unit; a last wave of at most
+//        a quarter runs as 128 sub-tiles;
+//   128: 4 (with the mirrored store; update 1.5) + 0.0098 K;
+//   64:  1.1 + 0.0039 K;   32 (one wave): 0.5 + 0.0021 K.
+// Up to three blocks of 128 or 64 share a unit, so at most 768 start at once and
+// the unit with the most of them ends last (528 of 64 with K = 2048: 23 us, 496
+// with 1984: 16 us); more are dealt out as units come free.
+double launch_us(int kind, int cfg, const std::vector<Item>& items, int segments) {
+  struct Cost {
+    double f, r, f1, r1;
+  };
+  const bool upd = kind == tmk::kKindUpdate;
+  const Cost cost[4] = {{13.0, 0.024, 13.0, 0.024},
+                        {upd ? 1.5 : 4.0, 0.0098, 4.5, 0.0095},
+                        {1.1, 0.0039, 3.2, 0.0029},
+                        {0.5, 0.0021, 0.5, 0.0021}};
+  const Cost& c = cost[cfg];
+  double sum = 0.0, tiles = 0.0, one = 0.0;
+  for (const Item& it : items) {
+    const double K = double(segments) * (kind == tmk::kKindGram ? it.Np : it.kp);
+    const double n = double(it.count) * tmk::blocks_per_matrix(kind, cfg, it.k, it.N, it.kp, it.Np);
+    tiles += n;
+    sum += n * (c.f + c.r * K);
+    one = std::max(one, c.f1 + c.r1 * K);
+  }
+  if (tiles == 0.0) return 0.0;
+  const double waves = std::floor(tiles / 256.0), frac = tiles / 256.0 - waves;
+  if (cfg == 0 && tiles > 256.0)
+    return sum / tiles * (waves + (frac == 0.0 ? 0.0 : (frac <= 0.25 ? 0.45 : 1.0)));
+  if ((cfg == 1 || cfg == 2) && tiles <= 768.0)
+    return std::max(one, c.f + (sum / tiles - c.f) * std::ceil(tiles / 256.0));
+  return std::max(one, sum / 256.0);
+}
+
+// The tile of a launch: cfg first .. last from the largest tile down, a
+// smaller one where the model puts it 10% ahead (within that, the larger tile
+// measured better: the 64 conv matrices' Gram on 240 tiles of 128 against 800
+// of 64 by 9%).
+int choose_cfg(int kind, int first, int last, const std::vector<Item>& items, int segments) {
+  int best = first;
+  double us = launch_us(kind, first, items, segments);
+  for (int cfg = first + 1; cfg <= last; ++cfg) {
+    const double t = launch_us(kind, cfg, items, segments);
+    if (t < 0.95 * us) {
+      best = cfg;
+      us = t;
+    }
+  }
+  return best;
+}
+
+// The layout tile of a call (its update's; the Gram and the k x k products may
+// run smaller ones): of the tiles whose zero padding adds at most 30% to the
+// call's products (the smallest always), the one with the shortest iteration, a
+// smaller one again from 5% on.  One 4096 x 4096 fp32 matrix: 256 tiles of 256,
+// one wave, instead of 1024 of 128; 1984 x 3072: 64 tiles without padding, whose
+// Gram and polynomial save more than the update loses.
+int choose_tile_cfg(const std::vector<Item>& items, int segments) {
   double real = 0.0;
   for (const Item& it : items)
     real += double(it.count) * (3.0 * it.k * double(it.k) * it.N + double(it.k) * it.k * it.k);
-  for (int cfg = 0; cfg < tmk::kNumCfg - 1; ++cfg) {
-    const uint32_t T = uint32_t(tmk::cfg_tile(cfg));
-    double padded = 0.0, tiles = 0.0, ksum = 0.0;
-    for (const Item& it : items) {
-      uint32_t kp, Np;
-      tmk::tiled_dims(it.k, it.N, T, &kp, &Np);
-      padded += double(it.count) * (3.0 * kp * double(kp) * Np + double(kp) * kp * kp);
-      const double t = double(it.count) * (kp / T) * (Np / T);
-      tiles += t;
-      ksum += t * kp;
+  int best = -1;
+  double us = 0.0;
+  for (int cfg = 0; cfg < tmk::kNumCfg; ++cfg) {
+    std::vector<Item> laid = items;
+    double padded = 0.0;
+    bool pairs = false;
+    for (Item& it : laid) {
+      tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(cfg)), &it.kp, &it.Np);
+      padded += double(it.count) * (3.0 * it.kp * double(it.kp) * it.Np + double(it.kp) * it.kp * it.kp);
+      pairs = pairs || it.pair;
     }
-    const bool long_k = T < 256 || ksum >= 512.0 * tiles;
-    if (padded <= 1.3 * real && tiles >= 480.0 && long_k) return cfg;
+    if (padded > 1.3 * real && cfg < tmk::kNumCfg - 1) continue;
+    auto shortest = [&](int kind) {
+      return launch_us(kind, choose_cfg(kind, cfg, tmk::kCfgSym32, laid, segments), laid, segments);
+    };
+    const double t = launch_us(tmk::kKindUpdate, cfg, laid, segments) +
+                     shortest(tmk::kKindGram) + (pairs ? 5.0 : 1.0) * shortest(tmk::kKindPoly);
+    if (best < 0 || t < 0.95 * us) {
+      best = cfg;
+      us = t;
+    }
   }
-  return tmk::kNumCfg - 1;
-}
-
-// bf16 Gram and polynomial phases: the layout tile T (kp, Np multiples of
-// it) is halved, down to 64 (or 32 with `small`: one-wave tiles, not for the
-// first Gram, whose row partials cover 64 columns), until the phase has one
-// and a half waves of tiles for the 256 compute units, or one wave at least
-// three quarters full (a tile per compute unit: no second, partly filled
-// wave); these phases have about k^2 / T^2 / 2 tiles per matrix against
-// k N / T^2 for the update.  (The 72 matrices of a 12-layer 768-wide model:
-// 432 tiles of 256 beat 1512 of 128 by 7% per call.)
-int choose_sym_cfg(int kind, int tcfg, const std::vector<Item>& items, bool small = false) {
-  int cfg = tcfg;
-  const int last = small ? tmk::kCfgSym32 : tmk::kNumCfg - 1;
-  while (cfg < last) {
-    uint64_t tiles = 0;
-    for (const Item& it : items)
-      tiles += uint64_t(it.count) * tmk::blocks_per_matrix(kind, cfg, it.k, it.N, it.kp, it.Np);
-    if (tiles >= 384 || (tiles >= 192 && tiles <= 256)) break;
-    ++cfg;
-  }
-  return cfg;
+  return best;
 }
 
 struct Plan {
@@ -235,41 +293,34 @@ struct Plan {
   int esz;
   hipStream_t st;
   int tcfg = 0;                   // bf16: the call's layout tile
+  std::vector<Item> shapes;       // shapes_of(items)
+  // tiles chosen so far for launches over all items of a class, by kind, smallest
+  // tile and classes (-1: none yet)
+  mutable int tile_of[tmk::kNumKinds][2][3];
   bool split = false;             // fp32 on fp16 planes (tm_fast.hip's kernels)
   bool timed = true;              // the timing hooks may bracket this call's launches
 };
 
-// bf16 update of one launch of a call split over several launches: the
-// largest tile (at most the layout tile) with about two waves of tiles.
-int choose_update_cfg(int tcfg, const std::vector<Item>& items) {
-  for (int cfg = tcfg; cfg < tmk::kNumCfg - 1; ++cfg) {
-    uint64_t tiles = 0;
-    for (const Item& it : items)
-      tiles += uint64_t(it.count) * tmk::blocks_per_matrix(tmk::kKindUpdate, cfg, it.k, it.N, it.kp, it.Np);
-    if (tiles >= 480) return cfg;
-  }
-  return tmk::kNumCfg - 1;
-}
-
 // Compute units of the MI355X: the blocks of one full wave of the large tiles.
 constexpr int kWave = 256;
 
-// K step (elements per ring stage) of a 4-wave or one-wave bf16 launch.  A
-// 96 KB ring (128 for the 64 tile, 64 for the 128 tile) holds one block per
-// compute unit, so it serves launches of at most one wave of blocks; a 48 KB
-// ring (64 for the 64 tile, 128 for the 32 tile) holds three, which suits a
-// launch of any size; else 32 (the 128 tile's many-block launches).  Every K
-// of the launch must be a multiple of the step: the Gram contracts over Np,
-// the polynomial and the update over kp.  (The 256 tile's ring is fixed.)
+// K step (elements per ring stage) of a 4-wave or one-wave launch.  A 96 KB
+// ring (128 for the 64 tile, 64 for the 128 tile) holds one block per compute
+// unit, so it serves launches of at most one wave of blocks; a 48 KB ring (64
+// for the 64 tile, 128 for the 32 tile) holds three, which suits a launch of
+// any size; else 32 (the 128 tile's many-block launches).  Every K of the
+// launch must be a multiple of the step (the Gram contracts over Np, the k x k
+// products and the update over kp): halved until it is.  (The 256 tile's ring
+// is fixed.)
 int k_step(int kind, int cfg, const Phase& P) {
   const int T = tmk::cfg_tile(cfg);
   int step = 32;
   if (T == 128 && P.total <= kWave) step = 64;
   if (T == 64) step = P.total <= kWave ? 128 : 64;
   if (T == 32) step = 128;
-  for (int e = 0; e < P.nent && step > 32; ++e) {
+  for (int e = 0; e < P.nent; ++e) {
     const uint32_t K = kind == tmk::kKindGram ? P.e[e].Np : P.e[e].kp;
-    if (P.e[e].tiles_per != 0u && K % uint32_t(step) != 0u) step = 32;
+    while (P.e[e].tiles_per != 0u && K % uint32_t(step) != 0u) step /= 2;
   }
   return step;
 }
@@ -321,14 +372,16 @@ struct Step {
   float alpha = 0.f, beta = 0.f, gamma = 0.f;
 };
 
-// Tile of one bf16 matrix-core launch over `items` (those it covers).  A call
-// that runs its update over all of its matrices in one launch keeps the
-// layout tile.
-int choose_step_cfg(int kind, uint32_t flags, int tcfg, const std::vector<Item>& items, bool whole) {
-  if (kind == tmk::kKindUpdate) return whole ? tcfg : choose_update_cfg(tcfg, items);
+// Tile of one matrix-core launch over `items` (those it covers), at most the
+// layout tile.  A call that runs its update over all of its matrices in one
+// launch keeps the layout tile.
+int choose_step_cfg(int kind, uint32_t flags, int tcfg, const std::vector<Item>& items, bool whole,
+                    int segments) {
+  if (kind == tmk::kKindUpdate)
+    return whole ? tcfg : choose_cfg(kind, tcfg, tmk::kNumCfg - 1, items, segments);
   // the first Gram's row partials and fp32 tiles want at least 64 columns
   const bool small = kind == tmk::kKindPoly || (flags & (tmk::kRowSum | tmk::kA32)) == 0u;
-  return choose_sym_cfg(kind, tcfg, items, small);
+  return choose_cfg(kind, tcfg, small ? tmk::kCfgSym32 : tmk::kNumCfg - 1, items, segments);
 }
 
 // One launch of `kind` per chunk of at most kMaxEntries entries and kMaxPtrs
@@ -385,13 +438,27 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     // launch of a split call may have much fewer); a product's arithmetic does
     // not depend on the tile size
     int ccfg = cfg;
-    if (steps != nullptr) {
+    if (steps != nullptr && chunks.size() == 1) {
+      const int classes = (steps[0] ? 1 : 0) + (steps[1] ? 2 : 0);
+      const bool small = (flags & (tmk::kRowSum | tmk::kA32)) == 0u;
+      int& memo = pl.tile_of[kind][small ? 1 : 0][classes - 1];
+      if (memo < 0) {
+        std::vector<Item> part;
+        for (const Item& it : pl.shapes)
+          if (covered(it)) part.push_back(it);
+        memo = part.empty() ? 0
+                            : choose_step_cfg(kind, flags, pl.tcfg, part,
+                                              part.size() == pl.shapes.size(), pl.split ? 3 : 1);
+      }
+      ccfg = memo;
+    } else if (steps != nullptr) {
       std::vector<Item> part;
       for (const Run& r : ch)
         for (size_t i = r.first; i < r.first + r.n; ++i)
           if (covered(items[idx[i]])) part.push_back(items[idx[i]]);
       if (part.empty()) continue;
-      ccfg = choose_step_cfg(kind, flags, pl.tcfg, part, part.size() == items.size());
+      ccfg = choose_step_cfg(kind, flags, pl.tcfg, shapes_of(part), part.size() == items.size(),
+                             pl.split ? 3 : 1);
     }
     uint64_t start = 0;
     uint32_t xp = 0;
@@ -672,15 +739,24 @@ bool half_ok(int iters, const float* coeffs, int precond, double top_b = 32.0) {
 // fewer operations still, but the Gram's rounding error then grows by a^2 for
 // every further iteration and passes the step-by-step form's on spectra with
 // many small singular values.
-// The line: measured, 8 x 4096 x 14336 20.0 -> 14.6 ms, the 64 conv matrices (N = 9 k)
-// 534 -> 427 us, one 768 x 3072 matrix 125 -> 122 us; square matrices do as many
-// operations either way and lose (8 x 4096 x 4096 7.4 -> 8.0 ms), N = 1.25 k saves 8%
-// of the operations.  Up to k = 32, one tile's k x k products are all latency.  The
-// matrices of the fused small-matrix kernel keep its step-by-step form.  The rule
-// depends on the shape alone, so that a matrix comes out the same from a single, a
-// batched and a grouped call.
+// The line.  Measured, step by step and in pairs: 8 x 4096 x 14336 20.0 and 14.6 ms,
+// 2 x 2048 x 8192 1.23 and 0.97 ms, 64 conv matrices (N = 9 k) 534 and 427 us, one
+// 768 x 3072 matrix 125 and 122 us; but 1 x 1984 x 3072 421 and 514 us, 40 x 200 x 300
+// 118 and 130 us, 8 x 4096 x 4096 7.4 and 8.0 ms.  Square matrices do as many operations
+// either way, and a product of two different k x k matrices reads twice the bytes of
+// A A, which the smaller tiles (k below 3072 or so) feel.  Below k = 1280 the k x k
+// products of a few matrices are all latency (6 us each whatever they do), of which a
+// pair has three more in place of a Gram and an update, and beside other matrices of
+// the call that go step by step the two chains share only some of their launches
+// (45 matrices, three of them 1819 x 547: 390 us step by step, 424 with those in
+// pairs): there the long side has to be much the longer, as in the MLPs of transformers
+// (4 k) and in 3 x 3 convolutions (9 k).  The rule depends on the shape alone, so that a
+// matrix comes out the same from a single, a batched and a grouped call.
 bool pair_rule(const Item& it) {
-  return it.k > 32 && 4 * uint64_t(it.N) >= 5 * uint64_t(it.k) && !small_eligible(it);
+  const uint64_t k = it.k, N = it.N;
+  if (k >= 3072) return 2 * N >= 3 * k;
+  if (k >= 1280) return N >= 2 * k;
+  return k >= 512 ? N >= 4 * k : (k >= 256 && N >= 9 * k);
 }
 
 // fp32 matrices on fp16 planes: 4096 x 4096 12.65 -> 4.9 ms, 256 x 256 162 -> 105 us,
@@ -838,9 +914,9 @@ tm_status plan_f32(const Plan& pl, int iters, const float* coeffs, int precond) 
     s = launch(pl, tmk::kKindTransposeIn, 0, 0, 0, 0.f, 0.f, 0.f, 0u, 0, kCoverTall);
     if (s != TM_OK) return s;
   }
-  const int gcfg = choose_cfg(tmk::kKindGram, items);
-  const int pcfg = choose_cfg(tmk::kKindPoly, items);
-  const int ucfg = choose_cfg(tmk::kKindUpdate, items);
+  const int gcfg = choose_cfg_f32(tmk::kKindGram, items);
+  const int pcfg = choose_cfg_f32(tmk::kKindPoly, items);
+  const int ucfg = choose_cfg_f32(tmk::kKindUpdate, items);
   const int part = tmk::cfg_tile(gcfg);   // row partials per Gram tile column block
 
   if (iters == 0) {
@@ -916,6 +992,24 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   Plan pl[2];
   uint64_t total = 0;
   const bool half = half_ok(iters, coeffs, precond);
+  // A call whose matrices are pairs but for some in the fused kernel's range runs
+  // those there, in one launch: step by step on tiles they would add about eight
+  // launches to the pairs' chain.  (Bit for bit the same results.)
+  if (esz == 2 && iters >= 2 && half && std::getenv("TM_DISABLE_FUSED") == nullptr) {
+    std::vector<Item> small, pairs;
+    for (const Item& it : items) (pair_rule(it) ? pairs : small).push_back(it);
+    if (!pairs.empty() && !small.empty() && std::all_of(small.begin(), small.end(), small_eligible)) {
+      Plan ps;
+      ps.items = &small;
+      ps.esz = esz;
+      ps.st = st;
+      ps.ws = nullptr;
+      ps.timed = ext_ws == nullptr;
+      s = plan_small(ps, iters, coeffs, precond);
+      if (s != TM_OK) return s;
+      items = pairs;
+    }
+  }
   const bool planes = esz == 4 && iters > 0 && half_ok(iters, coeffs, precond, 16.0);
   for (const Item& it : items) part[esz == 2 || (planes && split_rule(it)) ? 0 : 1].push_back(it);
   for (int p = 0; p < 2; ++p) {
@@ -925,10 +1019,10 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     pl[p].st = st;
     pl[p].split = p == 0 && esz == 4;
     if (p == 0) {
-      pl[p].tcfg = choose_tile_cfg(part[p]);
+      for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
+      pl[p].tcfg = choose_tile_cfg(shapes_of(part[p]), pl[p].split ? 3 : 1);
       for (Item& it : part[p]) {
         tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);
-        it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
         const int updates = it.pair ? (iters + 1) / 2 : iters;
         // A wide matrix that needs no padding is read in place by the first
         // update; a single update would read and write the caller's buffer in
@@ -939,6 +1033,8 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     } else {
       for (Item& it : part[p]) tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
     }
+    pl[p].shapes = shapes_of(part[p]);
+    std::memset(pl[p].tile_of, -1, sizeof(pl[p].tile_of));
     for (const Item& it : part[p]) {
       pl[p].ws_off.push_back(total);
       total += item_ws(it, esz);
@@ -1231,7 +1327,8 @@ uint64_t tm_workspace_bytes(const int64_t* m, const int64_t* n, int64_t count, i
       total += item_ws(it, dtype_bytes);
     }
   }
-  const int tcfg = tiled.empty() ? 0 : choose_tile_cfg(tiled);
+  for (Item& it : tiled) it.pair = dtype_bytes == 2 && pair_rule(it);
+  const int tcfg = tiled.empty() ? 0 : choose_tile_cfg(shapes_of(tiled), dtype_bytes == 4 ? 3 : 1);
   for (Item& it : tiled) {
     tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(tcfg)), &it.kp, &it.Np);
     total += item_ws(it, dtype_bytes);

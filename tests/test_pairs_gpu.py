@@ -1,5 +1,5 @@
-"""Two iterations per update (bf16, k > 32 and N >= 1.25 k outside the fused kernel's
-range): the k x k products of tm_fast.hip against the fp64 oracle at the edges of the tiles
+"""Two iterations per update (bf16, N at least 9 k from k = 256 on, 4 k from 512 on, 2 k
+from 1280 on and 1.5 k from 3072 on): the k x k products of tm_fast.hip against the fp64 oracle at the edges of the tiles
 and of the rule, for even and odd iteration counts, and equal bits from single, batched and
 grouped calls that run different tiles."""
 import numpy as np
@@ -21,10 +21,10 @@ def one(X, iters, precond, coeffs=None):
     return t
 
 
-# (k, N): the smallest k, tile remainders on either side, the ratio's edge (160 x 200 is
-# in, 161 x 200 is out), a k with several 64 tiles and a ragged N
-SHAPES = [(33, 1300), (63, 1111), (65, 1000), (128, 400), (160, 200), (161, 200),
-          (193, 777), (257, 513), (320, 1024)]
+# (k, N): the edges of the rule (256 x 2304, 512 x 2048 and 1280 x 2560 are in, 257 x 2304,
+# 513 x 2048 and 1281 x 2560 out), tile remainders on either side, ragged N
+SHAPES = [(256, 2304), (257, 2304), (300, 2701), (512, 2048), (513, 2048), (513, 2100),
+          (575, 2333), (577, 2900), (640, 3000), (1280, 2560), (1281, 2560)]
 
 
 @pytest.mark.parametrize("k,N", SHAPES)
@@ -50,13 +50,15 @@ def test_mixed_group_equals_single_calls_bitwise():
     matrices, with other tiles, than the single calls'."""
     log("case: mixed group vs single calls, bitwise")
     shapes = [(768, 3072), (515, 515), (64, 576), (129, 1153), (1001, 777), (300, 375), (2048, 640),
+              (1300, 2700),
               (768, 3072), (40, 41)]
     Xs = [make_input(m, n, 0.8, i, "bf16") for i, (m, n) in enumerate(shapes)]
-    for precond, iters in (("aol", 4), ("frobenius", 5), ("schatten4", 3)):
-        ts = [to_device(X, "bf16") for X in Xs]
+    for precond, iters, part in (("aol", 4, Xs), ("frobenius", 5, Xs), ("schatten4", 3, Xs),
+                                 ("aol", 4, [Xs[0], Xs[2], Xs[9]])):   # pairs and fused only
+        ts = [to_device(X, "bf16") for X in part]
         tm.orthogonalize_grouped(ts, iters, None, precond)
-        for i, X in enumerate(Xs):
-            assert torch.equal(ts[i], one(X, iters, precond)), (precond, shapes[i])
+        for i, X in enumerate(part):
+            assert torch.equal(ts[i], one(X, iters, precond)), (precond, X.shape)
 
 
 @pytest.mark.parametrize("scale", [30.0, 1e3])
@@ -64,7 +66,7 @@ def test_large_coefficients_stay_finite(scale):
     """Coefficients whose k x k matrices could leave fp16's range take the bf16
     step-by-step form: linear steps (scale, 0, 0) multiply by scale each."""
     log(f"case: linear steps of {scale}")
-    X = make_input(96, 400, 0.8, 5, "bf16")
+    X = make_input(520, 2100, 0.8, 5, "bf16")
     co = [(scale, 0.0, 0.0)] * 4
     G = from_device(one(X, 4, "aol", co))
     R = O.orthogonalize(X, 4, co, "aol")
@@ -76,17 +78,17 @@ def test_non_finite_input_stays_visible(bad):
     """One NaN or infinity reaches every output, as in the step-by-step form (its row sum
     scales every row)."""
     log(f"case: {bad} in the input")
-    X = make_input(128, 512, 0.8, 6, "bf16")
+    X = make_input(512, 2048, 0.8, 6, "bf16")
     X[5, 7] = bad
     assert np.isnan(from_device(one(X, 4, "aol"))).all()
 
 
 def test_zero_rows_and_zero_matrix():
     log("case: zero rows, zero matrix")
-    X = make_input(130, 520, 0.8, 7, "bf16")
+    X = make_input(530, 2200, 0.8, 7, "bf16")
     X[3] = 0.0
-    X[129] = 0.0
+    X[529] = 0.0
     G = from_device(one(X, 4, "aol"))
     R = O.orthogonalize(X, 4, None, "aol")
-    assert relF(G, R) <= BF16_TOL and not G[3].any() and not G[129].any()
+    assert relF(G, R) <= BF16_TOL and not G[3].any() and not G[529].any()
     assert not from_device(one(0.0 * X, 4, "frobenius")).any()
