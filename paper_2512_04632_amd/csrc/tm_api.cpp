@@ -995,20 +995,12 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   // A call whose matrices are pairs but for some in the fused kernel's range runs
   // those there, in one launch: step by step on tiles they would add about eight
   // launches to the pairs' chain.  (Bit for bit the same results.)
+  std::vector<Item> small;
   if (esz == 2 && iters >= 2 && half && std::getenv("TM_DISABLE_FUSED") == nullptr) {
-    std::vector<Item> small, pairs;
+    std::vector<Item> pairs;
     for (const Item& it : items) (pair_rule(it) ? pairs : small).push_back(it);
-    if (!pairs.empty() && !small.empty() && std::all_of(small.begin(), small.end(), small_eligible)) {
-      Plan ps;
-      ps.items = &small;
-      ps.esz = esz;
-      ps.st = st;
-      ps.ws = nullptr;
-      ps.timed = ext_ws == nullptr;
-      s = plan_small(ps, iters, coeffs, precond);
-      if (s != TM_OK) return s;
-      items = pairs;
-    }
+    if (!pairs.empty() && std::all_of(small.begin(), small.end(), small_eligible)) items = pairs;
+    else small.clear();
   }
   const bool planes = esz == 4 && iters > 0 && half_ok(iters, coeffs, precond, 16.0);
   for (const Item& it : items) part[esz == 2 || (planes && split_rule(it)) ? 0 : 1].push_back(it);
@@ -1051,6 +1043,16 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   } else {
     s = get_workspace(dev, st, size_t(total), &ws);
     if (s != TM_OK) return s;
+  }
+  // nothing is enqueued before this point, where the call can still fail
+  if (!small.empty()) {
+    Plan ps;
+    ps.items = &small;
+    ps.esz = esz;
+    ps.st = st;
+    ps.ws = nullptr;
+    ps.timed = ext_ws == nullptr;
+    s = plan_small(ps, iters, coeffs, precond);
   }
   for (int p = 0; p < 2 && s == TM_OK; ++p) {
     if (part[p].empty()) continue;

@@ -92,3 +92,19 @@ def test_zero_rows_and_zero_matrix():
     R = O.orthogonalize(X, 4, None, "aol")
     assert relF(G, R) <= BF16_TOL and not G[3].any() and not G[529].any()
     assert not from_device(one(0.0 * X, 4, "frobenius")).any()
+
+
+def test_failed_allocation_leaves_a_mixed_group_untouched(monkeypatch):
+    """Pairs beside matrices of the fused range, which need no workspace: still nothing is
+    enqueued when the pairs' workspace cannot be had."""
+    log("case: forced workspace allocation failure, 768 x 3072 and 64 x 576")
+    Xs = [make_input(768, 3072, 0.8, 1, "bf16"), make_input(64, 576, 0.8, 2, "bf16")]
+    ts = [to_device(X, "bf16") for X in Xs]
+    keep = [t.clone() for t in ts]
+    torch.cuda.synchronize()
+    tm.release_workspaces()
+    monkeypatch.setenv("TM_TEST_FAIL_ALLOC", "1")
+    with pytest.raises(tm.TurboMuonError):
+        tm.orthogonalize_grouped(ts, 4, None, "aol")
+    torch.cuda.synchronize()
+    assert all(torch.equal(t, k) for t, k in zip(ts, keep))
