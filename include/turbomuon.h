@@ -21,13 +21,15 @@
  *
  * Arithmetic.  bf16 entry points store X, A and B in bfloat16 (round to
  * nearest even) and accumulate every product in fp32 on the matrix cores; the
- * AOL row sums are taken from the fp32 Gram accumulators.  Two iterations of a
- * matrix with max(m, n) >= 1.25 min(m, n) share one Gram and one update, with
- * fp16 A, B between them (a smaller error than one by one; calls whose
- * coefficients could leave fp16's range, and precond NONE, run one by one).
- * f32 entry points store in fp32 and accumulate in fp32; matrices with
- * min(m, n) >= 64 are multiplied as two fp16 planes of 22 bits or more, scaled
- * row by row, the others (and the calls named above) in fp32.  Results are deterministic: no float atomics.
+ * AOL row sums are taken from the fp32 Gram accumulators.  Where the long side
+ * is much the longer (max(m, n) at least 9 min(m, n) from min(m, n) = 256 on,
+ * 4 from 512, 2 from 1280 and 1.5 from 3072 on), two iterations share one Gram
+ * and one update, with fp16 A, B between them (a smaller error than one by one;
+ * calls whose coefficients could leave fp16's range, and precond NONE, run one
+ * by one).  f32 entry points store in fp32 and accumulate in fp32; matrices
+ * with min(m, n) >= 64 are multiplied as two fp16 planes of 22 bits or more,
+ * scaled row by row, the others (and the calls named above) in fp32.  Results
+ * are deterministic: no float atomics.
  *
  * Small matrices.  A bf16 call with iters >= 1 whose every matrix has
  * min(m, n) <= 128 and fits, zero padded to multiples of 32, in one compute

@@ -286,6 +286,29 @@ int choose_tile_cfg(const std::vector<Item>& items, int segments) {
   return best;
 }
 
+// Workspace of `shapes` laid out on a tile size.
+uint64_t laid_bytes(std::vector<Item> shapes, int cfg, int esz) {
+  uint64_t total = 0;
+  for (Item& it : shapes) {
+    tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(cfg)), &it.kp, &it.Np);
+    total += item_ws(it, esz);
+  }
+  return total;
+}
+
+// The layout tile with the static scratch of the allocation-free entry point
+// in view: a bf16 call that fits it on a smaller tile takes that one, whichever
+// entry point it came by (equal launches, and tm_workspace_bytes tells which
+// calls fit).  4 x 1044 x 1480: 67.8 MB on 128 tiles, 61.9 on 64; near the
+// limit the padding of the larger tile is what decides.
+int layout_cfg(const std::vector<Item>& shapes, int esz) {
+  constexpr uint64_t kLimit = TM_NOALLOC_SCRATCH_BYTES;
+  int cfg = choose_tile_cfg(shapes, esz == 4 ? 3 : 1);
+  if (esz == 2 && laid_bytes(shapes, tmk::kNumCfg - 1, esz) <= kLimit)
+    while (laid_bytes(shapes, cfg, esz) > kLimit) ++cfg;
+  return cfg;
+}
+
 struct Plan {
   const std::vector<Item>* items;
   std::vector<uint64_t> ws_off;   // byte offset of each item's workspace region
@@ -1012,7 +1035,7 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     pl[p].split = p == 0 && esz == 4;
     if (p == 0) {
       for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
-      pl[p].tcfg = choose_tile_cfg(shapes_of(part[p]), pl[p].split ? 3 : 1);
+      pl[p].tcfg = layout_cfg(shapes_of(part[p]), esz);
       for (Item& it : part[p]) {
         tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);
         const int updates = it.pair ? (iters + 1) / 2 : iters;
@@ -1329,12 +1352,23 @@ uint64_t tm_workspace_bytes(const int64_t* m, const int64_t* n, int64_t count, i
       total += item_ws(it, dtype_bytes);
     }
   }
-  for (Item& it : tiled) it.pair = dtype_bytes == 2 && pair_rule(it);
-  const int tcfg = tiled.empty() ? 0 : choose_tile_cfg(shapes_of(tiled), dtype_bytes == 4 ? 3 : 1);
-  for (Item& it : tiled) {
-    tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(tcfg)), &it.kp, &it.Np);
-    total += item_ws(it, dtype_bytes);
+  if (tiled.empty()) return total;
+  // The tile depends on the form that iters and coeffs give the call: step by
+  // step, with pairs, and pairs without the matrices of the fused kernel.
+  auto bytes = [&](const std::vector<Item>& part) {
+    const std::vector<Item> shapes = shapes_of(part);
+    return shapes.empty() ? 0 : laid_bytes(shapes, layout_cfg(shapes, dtype_bytes), dtype_bytes);
+  };
+  uint64_t most = bytes(tiled);
+  if (dtype_bytes == 2) {
+    std::vector<Item> pairs;
+    for (Item& it : tiled) {
+      it.pair = pair_rule(it);
+      if (it.pair) pairs.push_back(it);
+    }
+    most = std::max(most, std::max(bytes(tiled), bytes(pairs)));
   }
+  total += most;
   return total;
 }
 

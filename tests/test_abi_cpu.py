@@ -127,6 +127,14 @@ def test_workspace_bytes():
     assert tm.workspace_bytes([(4, 4)], 3) == 0
 
 
+@pytest.mark.parametrize("m,n,batch", [(1044, 1480, 4), (1535, 1073, 4), (473, 15177, 2), (9336, 698, 2),
+                                       (2079, 3433, 1), (703, 839, 9), (1546, 1768, 2)])
+def test_calls_that_fit_the_static_scratch_on_some_tile_fit_it(m, n, batch):
+    """Padded to multiples of 64 these fit in the allocation-free call's scratch, on larger
+    tiles not: the layout must not refuse them there."""
+    assert tm.workspace_bytes([(m, n)] * batch, 2) <= tm.TM_NOALLOC_SCRATCH_BYTES
+
+
 def test_muon_step_validation():
     f = tm.lib().tm_muon_step_grouped
     P3 = ctypes.c_void_p * 2
