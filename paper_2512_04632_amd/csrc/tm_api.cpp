@@ -334,13 +334,19 @@ constexpr int kWave = 256;
 // any size; else 32 (the 128 tile's many-block launches).  Every K of the
 // launch must be a multiple of the step (the Gram contracts over Np, the k x k
 // products and the update over kp): halved until it is.  (The 256 tile's ring
-// is fixed.)
-int k_step(int kind, int cfg, const Phase& P) {
+// is fixed.)  A symmetric fp32 launch of different lengths also takes the 96 KB
+// ring up to two waves of 64 tiles: its long tiles (three K segments) then have a
+// unit each and the short ones fill the units as they come free (468 tiles 526 -> 519
+// us a call, 486 tiles 687 -> 630; but 752 tiles 843 -> 867, and bf16's
+// short ones gain nothing, 494 -> 552).
+int k_step(int kind, int cfg, const Phase& P, bool split) {
   const int T = tmk::cfg_tile(cfg);
   int step = 32;
   if (T == 128 && P.total <= kWave) step = 64;
   if (T == 64) step = P.total <= kWave ? 128 : 64;
   if (T == 32) step = 128;
+  if (split && T == 64 && (P.flags & tmk::kBySlice) && kind != tmk::kKindUpdate && P.total <= 2 * kWave)
+    step = 128;
   for (int e = 0; e < P.nent; ++e) {
     const uint32_t K = kind == tmk::kKindGram ? P.e[e].Np : P.e[e].kp;
     while (P.e[e].tiles_per != 0u && K % uint32_t(step) != 0u) step /= 2;
@@ -366,9 +372,9 @@ tm_status fire(const Plan& pl, int kind, int cfg, const Phase& P) {
   else if (elementwise)
     e = tmk::launch_elementwise_bf16(kind, P, pl.st);
   else if (pl.split)
-    e = tmk::launch_split_f32(kind, cfg, k_step(kind, cfg, P), P, pl.st);
+    e = tmk::launch_split_f32(kind, cfg, k_step(kind, cfg, P, pl.split), P, pl.st);
   else
-    e = tmk::launch_fast_bf16(kind, cfg, k_step(kind, cfg, P), P, pl.st);
+    e = tmk::launch_fast_bf16(kind, cfg, k_step(kind, cfg, P, pl.split), P, pl.st);
   if (tl.start) {
     (void)hipEventRecord(tl.stop, pl.st);
     g_timed.push_back(tl);
@@ -418,16 +424,19 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     return !((cover == kCoverTall && !it.tall) || (cover == kCoverCopied && it.direct) ||
              (steps != nullptr && steps[it.pair ? 1 : 0] == nullptr));
   };
-  // update launches take their largest products first (the longest tiles
-  // start first); every entry carries its own workspace offset
+  // Long tiles start first: update launches take their largest products first,
+  // the symmetric ones their longest contractions (a group whose long ones come
+  // last otherwise ends on them: 30 x 256 x 256 beside 3 x 1500 x 1700, 493 -> 422
+  // us a call).  Every entry carries its own workspace offset.
   std::vector<size_t> idx(items.size());
   for (size_t i = 0; i < idx.size(); ++i) idx[i] = i;
-  if (kind == tmk::kKindUpdate)
-    std::stable_sort(idx.begin(), idx.end(), [&](size_t x, size_t y) {
-      const Item& u = items[x];
-      const Item& v = items[y];
-      return double(u.k) * u.k * u.N * u.count > double(v.k) * v.k * v.N * v.count;
-    });
+  auto length = [&](const Item& it) {
+    return kind == tmk::kKindUpdate ? double(it.k) * it.k * it.N * it.count
+                                    : double(kind == tmk::kKindGram ? it.Np : it.kp);
+  };
+  if (kind == tmk::kKindUpdate || steps != nullptr)
+    std::stable_sort(idx.begin(), idx.end(),
+                     [&](size_t x, size_t y) { return length(items[x]) > length(items[y]); });
   auto joins = [&](size_t prev, size_t next) {
     const Item& u = items[idx[prev]];
     const Item& v = items[idx[next]];
@@ -534,15 +543,18 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     P.aux = aux;
     P.tail_base = 0;
     tm_status s = TM_OK;
-    // A bf16 matrix-core launch whose entries' tiles differ in K deals whole
-    // matrices round-robin to the XCDs (kByMatrix) when that splits the work
-    // evenly (every XCD within 10% of an eighth, the cost of a tile taken as
-    // its K): the default chunks of consecutive tiles per XCD would give the
-    // first XCDs all the long tiles of a largest-first launch.  A launch of a
-    // few matrices keeps the chunks.
-    const bool mc0 = kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate;
-    bool by_matrix = false;
-    if ((pl.esz == 2 || pl.split) && mc0) {
+    // A matrix-core launch whose entries' tiles differ in K gives every XCD an
+    // eighth of each entry (kBySlice): the default chunks of consecutive tiles
+    // would give the first XCDs all the long tiles of the launch.  us a call,
+    // chunks and slices, both sorted: 30 x 256 x 256 with 3 x 1500 x 1700 422 and
+    // 409; 6 x 2048 x 2048 with 4 of 2048 x 5632 2725 and 2640; dealing whole
+    // matrices out in turn, where that is even, measures the same as slices (72
+    // GPT-2 and 64 conv matrices within 0.4%).  Slices also stand in for the
+    // sub-tiles of a nearly empty last wave (below), where the shortest tiles are
+    // last: 20 x 1024 x 1024 with 8 x 1024 x 1800 902 us, with sub-tiles 952.
+    const bool mc = kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate;
+    bool by_slice = false;
+    if ((pl.esz == 2 || pl.split) && mc) {
       uint32_t kmin = UINT32_MAX, kmax = 0;
       for (int e = 0; e < P.nent; ++e) {
         if (P.e[e].tiles_per == 0u) continue;
@@ -550,40 +562,15 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
         kmin = std::min(kmin, K);
         kmax = std::max(kmax, K);
       }
-      if (kmin != kmax) {
-        uint64_t q[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        double cost[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        uint64_t g0 = 0;
-        for (int e = 0; e < P.nent; ++e) {
-          const uint64_t c = P.e[e].count;
-          const double K = kind == tmk::kKindGram ? P.e[e].Np : P.e[e].kp;
-          for (int x = 0; x < 8; ++x) {
-            const uint64_t i0 = uint64_t((x - int(g0 & 7u) + 8) & 7);
-            const uint64_t t = (i0 < c ? (c - 1 - i0) / 8 + 1 : 0) * P.e[e].tiles_per;
-            q[x] += t;
-            cost[x] += double(t) * K;
-          }
-          g0 += c;
-        }
-        double sum = 0.0, top = 0.0;
-        for (int x = 0; x < 8; ++x) {
-          sum += cost[x];
-          top = std::max(top, cost[x]);
-        }
-        if (top <= 1.1 * sum / 8.0) {
-          P.flags |= tmk::kByMatrix;
-          P.total = int32_t(8 * *std::max_element(q, q + 8));
-          by_matrix = true;
-        }
-      }
+      by_slice = kmin < kmax;
+      if (by_slice) P.flags |= tmk::kBySlice;
     }
     // bf16 matrix-core phases on 256 x 256 tiles whose last wave would be at
     // most a quarter full: the full waves run as usual, the remaining tiles as
     // 2 x 2 sub-tiles of 128 x 128 in a second launch that fits in one wave
     // (same per-element arithmetic, four times the blocks for the idle units);
     // an update tail of at most 16 tiles as 4 x 4 sub-tiles of 64 x 64.
-    const bool mc = kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate;
-    const int tail = (!by_matrix && (pl.esz == 2 || pl.split) && ccfg == 0 && mc && P.total > kWave && P.total % kWave <= kWave / 4)
+    const int tail = (!by_slice && (pl.esz == 2 || pl.split) && ccfg == 0 && mc && P.total > kWave && P.total % kWave <= kWave / 4)
                          ? P.total % kWave
                          : 0;
     if (tail > 0) {

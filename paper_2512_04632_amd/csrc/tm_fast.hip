@@ -827,26 +827,27 @@ __device__ inline Loc locate(const Phase& P, int lid) {
   return L;
 }
 
-// kByMatrix: workgroup p runs on XCD p % 8 (round-robin dispatch), and XCD x's
-// workgroups take, in launch order, the tiles of the launch's matrices whose
-// index is x mod 8: each XCD gets an eighth of every kind of matrix (balanced
-// when tile costs differ between entries) and a matrix's tiles share one L2.
-// False for the workgroups past the end of their XCD's list.
-__device__ inline bool locate_by_matrix(const Phase& P, int p, Loc& L) {
+// kBySlice: workgroup p runs on XCD p % 8, and XCD x's workgroups take, entry
+// after entry, a contiguous eighth of the entry's tiles (balanced when tile
+// costs differ between entries); the remainders go to the XCDs in turn, so XCD
+// x's share is exactly its total / 8 (one more for x < total % 8) workgroups.
+// False past the end of the list.
+__device__ inline bool locate_by_slice(const Phase& P, int p, Loc& L) {
   const int x = p & 7;
-  int j = p >> 3, g0 = 0;
+  int j = p >> 3, turn = 0;
   for (int e = 0; e < P.nent; ++e) {
-    const int c = int(P.e[e].count), tp = int(P.e[e].tiles_per);
-    const int i0 = (x - (g0 & 7) + 8) & 7;        // first matrix of the entry on XCD x
-    const int nt = (i0 < c ? (c - 1 - i0) / 8 + 1 : 0) * tp;
+    const int tp = int(P.e[e].tiles_per), n = int(P.e[e].count) * tp;
+    const int y = (x - turn) & 7, rest = n & 7;   // this XCD's place in the entry's order
+    const int nt = (n >> 3) + (y < rest ? 1 : 0);
     if (j < nt) {
       L.E = scalar(P.e[e]);
-      L.mat = i0 + 8 * (j / tp);
-      L.tile = j - (j / tp) * tp;
+      const int r = y * (n >> 3) + min(y, rest) + j;
+      L.mat = r / tp;
+      L.tile = r - L.mat * tp;
       return true;
     }
     j -= nt;
-    g0 += c;
+    turn += rest;
   }
   return false;
 }
@@ -925,8 +926,8 @@ __device__ inline bool sym_tile(const Phase& P, Loc& L, int& I, int& J) {
     J = 2 * J2 + (sub & 1);
     return true;
   }
-  if (P.flags & kByMatrix) {
-    if (!locate_by_matrix(P, int(blockIdx.x), L)) return false;
+  if (P.flags & kBySlice) {
+    if (!locate_by_slice(P, int(blockIdx.x), L)) return false;
   } else {
     L = locate(P, xcd_remap(blockIdx.x, P.total));
   }
@@ -1462,8 +1463,9 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
   const int FF = F * F;
   Loc L;
   if (tail) L = locate(P, P.tail_base + int(blockIdx.x) / FF);
-  else if (!(P.flags & kByMatrix)) L = locate(P, xcd_remap(blockIdx.x, P.total));
-  else if (!locate_by_matrix(P, int(blockIdx.x), L)) return;
+  else if (P.flags & kBySlice) {
+    if (!locate_by_slice(P, int(blockIdx.x), L)) return;
+  } else L = locate(P, xcd_remap(blockIdx.x, P.total));
   const Entry& E = L.E;
   const int kp = int(E.kp), Np = int(E.Np), k = int(E.k), N = int(E.N);
   const int TL = F * T;

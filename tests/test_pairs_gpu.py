@@ -108,3 +108,23 @@ def test_failed_allocation_leaves_a_mixed_group_untouched(monkeypatch):
         tm.orthogonalize_grouped(ts, 4, None, "aol")
     torch.cuda.synchronize()
     assert all(torch.equal(t, k) for t, k in zip(ts, keep))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shapes", [
+    [(70, 100), (100, 1500), (300, 310)],                        # fewer tiles than XCDs in an entry
+    [(200, 260)] * 9 + [(1000, 600)] + [(130, 2000)] * 3,        # the longest products last
+    [(300, 500)] * 20 + [(500, 1999)] * 5 + [(1000, 1200)] * 2,  # more than two waves of tiles
+])
+def test_mixed_lengths_equal_single_calls_bitwise(dtype, shapes):
+    """Entries of different K in one launch: every XCD takes an eighth of each, the long ones
+    first; a tile left out or done for another matrix would show in the bits."""
+    log(f"case: mixed lengths {dtype}, {len(shapes)} matrices, the last {shapes[-1]}")
+    ts = [to_device(make_input(m, n, 0.8, 40 + i, dtype), dtype) for i, (m, n) in enumerate(shapes)]
+    ref = [t.clone() for t in ts]
+    tm.orthogonalize_grouped(ts, 3, None, "aol")
+    for t, r in zip(ts, ref):
+        tm.orthogonalize(r, 3, None, "aol")
+    torch.cuda.synchronize()
+    for i, (t, r) in enumerate(zip(ts, ref)):
+        assert torch.equal(t, r), i
