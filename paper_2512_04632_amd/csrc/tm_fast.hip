@@ -1694,8 +1694,8 @@ __global__ __launch_bounds__(256) void k_row_max(const Phase P) {
 
 // W1 = the planes of X (wide) or X^T (tall), zero padded: row i scaled by
 // kScaleY 2^-e with 2^(e - 1) <= the row's largest magnitude < 2^e, so that
-// rows of any size keep their bits; r_i = 2^e / kScaleY is kept for the first
-// Gram and polynomial.  One block per 64 x 64 tile.
+// rows of any size keep their bits; r_i = 2^e / kScaleY (0 for a zero row) is
+// kept for the first Gram and polynomial.  One block per 64 x 64 tile.
 __global__ __launch_bounds__(256) void k_load_split(const Phase P) {
   __shared__ float tile[64][65];
   __shared__ float up[64];
@@ -1716,11 +1716,15 @@ __global__ __launch_bounds__(256) void k_load_split(const Phase P) {
     float m = 0.f;
 #pragma unroll 4
     for (int q = 0; q < nch; ++q) m = fmaxf(m, pm[int64_t(q) * E.kp]);
-    // exponent e, held in [-100, 128] so that both scales are normal numbers;
-    // an all-zero row keeps e = 0
+    // exponent e, held in [-100, 128] so that both scales are normal numbers.
+    // An all-zero row has r = 0: any other value would meet the uniform s of
+    // Frobenius and Schatten-4, which grows without bound as the norm falls, on
+    // the diagonal of the first factor, a s r kScaleY (infinite in fp16 from
+    // s = 19 on with r kScaleY = 1); of other rows s r kScaleY is at most 2.
     const int e = m > 0.f ? min(max(int(__float_as_uint(m) >> 23) - 126, -100), 128) : 0;
     up[threadIdx.x] = __uint_as_float(uint32_t(127 + 14 - e) << 23);
-    if (tl == 0) row_scale(w, WL, E)[ti * 64 + threadIdx.x] = __uint_as_float(uint32_t(127 - 14 + e) << 23);
+    if (tl == 0)
+      row_scale(w, WL, E)[ti * 64 + threadIdx.x] = m > 0.f ? __uint_as_float(uint32_t(127 - 14 + e) << 23) : 0.f;
   }
   // tile row r: X row ti 64 + r (wide) or tl 64 + r (tall), columns from the
   // other tile index; all loads of a thread in flight, none behind a branch

@@ -86,3 +86,19 @@ def test_non_finite_input_stays_visible(bad):
     X = make_input(96, 300, 0.8, 6, "f32")
     X[5, 7] = bad
     assert np.isnan(one(X, 4, "aol")).all()
+
+
+@pytest.mark.parametrize("precond,iters", [("frobenius", 1), ("frobenius", 4), ("schatten4", 1), ("schatten4", 4)])
+@pytest.mark.parametrize("tall", [False, True])
+@pytest.mark.parametrize("norm", [1e-3, 1e-7, 1.0, 1e6])   # norm^4, the Schatten-4 sum, is a normal fp32 number
+def test_zero_rows_of_matrices_of_any_norm(precond, iters, tall, norm):
+    """A uniform scale of 1 / norm reaches the zero rows too (a dead unit): the first factor's
+    diagonal there is a s r kScaleY, which must stay finite in fp16 for any norm."""
+    log(f"case: zero rows, {precond} t={iters} tall={tall} norm={norm}")
+    X = make_input(100, 330, 0.8, 11, "f32")
+    X = (X * (norm / np.linalg.norm(X))).astype(np.float32).astype(np.float64)
+    X[[0, 63, 64, 99]] = 0.0
+    G = one(X.T if tall else X, iters, precond)
+    G = G.T if tall else G
+    assert np.isfinite(G).all() and not G[[0, 63, 64, 99]].any()
+    assert relF(G, O.orthogonalize(X, iters, None, precond)) <= TOL
