@@ -1418,8 +1418,9 @@ __device__ __forceinline__ void sym_block(const Phase& P, const Entry& E, char* 
   uint16_t* out = kbuf(w, WL, op.out());
   auto val = [=](int i, int j, float x, uint16_t mij) __attribute__((always_inline)) {
     const float m = hasm ? (H ? h2f(mij) : bf2f(mij)) : 0.f;
-    // spelled out, so that every kernel that forms B~ rounds it alike
-    return __builtin_fmaf(be, m, al * x) + ((diag && i == j) ? ga : 0.f);
+    // spelled out, so that every kernel that forms B~ rounds it alike: b A, then
+    // the fused c A A (the other way round some B~ come out one bf16 unit apart)
+    return __builtin_fmaf(al, x, be * m) + ((diag && i == j) ? ga : 0.f);
   };
   if constexpr (MODE == kSymBf16Scaled || MODE == kSymFactorScaled)
     epilogue_sym_scaled<T>(acc, smem, out, ldg, I, J, upper, val, reinterpret_cast<const float*>(w + WL.s));

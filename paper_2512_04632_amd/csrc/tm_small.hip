@@ -609,7 +609,8 @@ __global__ __launch_bounds__(64 * NW) void k_small_ns(const SmallPhase P) {
           uint16_t o[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const float x = __builtin_fmaf(cb, bf2f(av[u]), cc * acc[fm][fn][u]) + (i0 + u == j ? ca : 0.f);
+            // rounded in the order of the tiled kernels: b A, then the fused c A A
+            const float x = __builtin_fmaf(cc, acc[fm][fn][u], cb * bf2f(av[u])) + (i0 + u == j ? ca : 0.f);
             // stored at (j, i0 + u): B~ is symmetric; C[j][i] = B~_ij s_i
             o[u] = f2bf(first && scaled ? x * G.s[i0 + u] : x);
           }

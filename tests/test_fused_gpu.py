@@ -266,3 +266,24 @@ def test_fused_large_batch_of_tiny_matrices():
     assert torch.equal(f.view(torch.int16), t.view(torch.int16))
     e = relF(from_device(f[65536]), O.orthogonalize(from_device(X[65536]), 4, None, "aol"))
     assert e <= BF16_TOL
+
+
+def test_polynomial_rounds_b_a_before_the_fused_c_a_a():
+    """1 x 1 matrices, one unscaled step with a = 0 and b A almost cancelled by c A A: the order
+    of the two roundings shows in the bits, emulated here from the formats (every other product
+    of the step is exact in fp32)."""
+    def bf16(v):
+        return torch.from_numpy(v.astype(np.float32)).bfloat16().float().numpy()
+
+    x = bf16(np.linspace(0.5, 3.0, 200))
+    A = bf16(x * x)                                         # x x: 16 bits
+    for q in range(24):
+        c = np.float32(1.0 + q / 7.0)
+        b = np.float32(-c * A[8 * q] * (1.0 + 2.0 ** -19))  # cancels at this A
+        s = (np.float64(c) * np.float64(A * A) + np.float64(b * A)).astype(np.float32)
+        want = torch.from_numpy(bf16(s) * x).bfloat16()
+        for path in (contextlib.nullcontext(), tiled_only()):
+            t = torch.from_numpy(x).bfloat16().reshape(-1, 1, 1).cuda()
+            with path:
+                tm.orthogonalize(t, 1, [(0.0, float(b), float(c))], "none")
+            assert torch.equal(t.cpu().reshape(-1), want), q
