@@ -1219,17 +1219,57 @@ __device__ inline f32x4_t fresh(f32x4_t x) {
   return x;
 }
 
-// Symmetric product: f(i_local, j_local, acc block, v) fills the values of 4
+// Symmetric product: f(i_local, j_local, acc block, which, v) fills the values of 4
 // consecutive rows i of column j; the tile goes out plane by plane as rows of
 // tile (J, I) (element (j, i)) and, off the diagonal, transposed as tile
-// (I, J).  With two values per element (scaled: the mirror's and the tile's
-// differ) f is asked for each, which = 0, 1.
+// (I, J).  With two values per element (TWO: the mirror's and the tile's
+// differ) f is asked for each, which = 0, 1.  A diagonal tile is the upper half
+// of the accumulators and its mirror: the two cross segments of (i, j) and
+// (j, i) run in the other order, and a smaller tile would hold only (i, j).
 template <int T, bool TWO, class Fv>
 __device__ __forceinline__ void epilogue_split(const AccT<T>& acc, char* st, uint16_t* D, int64_t lo,
                                                int64_t ld, int I, int J, Fv f) {
   const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
+  if (I == J) {
+    const int lr = 4 * ((threadIdx.x & 63) >> 4), lc = threadIdx.x & 15;   // place within a block
 #pragma unroll 1
-  for (int q = 0; q < (TWO && I != J ? 4 : 2); ++q) {
+    for (int q = 0; q < (TWO ? 4 : 2); ++q) {   // both values of a plane, then its rows
+      const int p = TWO ? q >> 1 : q, which = TWO ? q & 1 : 0;
+      if (q > 0) __syncthreads();
+#pragma unroll
+      for (int fm = 0; fm < Tile<T>::FM; ++fm)
+#pragma unroll
+        for (int fn = 0; fn < Tile<T>::FN; ++fn) {
+          const int over = wn * Tile<T>::TWN + fn * 16 - (wm * Tile<T>::TWM + fm * 16);
+          if (over < 0) continue;   // a block below the diagonal
+          const int c = acc_col<T>(wn, fn);
+          const int r0 = acc_row<T>(wm, fm);
+          float v[4];
+          f(r0, c, fresh(acc[fm][fn]), which, v);
+          uint32_t o[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) o[u] = plane_of(v[u], p);
+          // a wave's LDS writes land in order: in a 16 x 16 block on the diagonal
+          // the mirror replaces what the vector wrote above it
+          if (which == 0)
+            *reinterpret_cast<uint2*>(st + c * Stage<T>::RS + r0 * 2) =
+                make_uint2(o[0] | o[1] << 16, o[2] | o[3] << 16);
+          asm volatile("" ::: "memory");   // in this order, whatever their types
+          if (!TWO || which == 1)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (over > 0 || lr + u < lc)
+                *reinterpret_cast<uint16_t*>(st + (r0 + u) * Stage<T>::RS + c * 2) = uint16_t(o[u]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      if (TWO && which == 0) continue;
+      __syncthreads();
+      store_rows<T>(st, D + p * lo, ld, int64_t(J) * T, int64_t(I) * T);
+    }
+    return;
+  }
+#pragma unroll 1
+  for (int q = 0; q < (TWO ? 4 : 2); ++q) {
     const int p = q & 1, which = q >> 1;
     if (q > 0) __syncthreads();
 #pragma unroll
@@ -1248,7 +1288,7 @@ __device__ __forceinline__ void epilogue_split(const AccT<T>& acc, char* st, uin
     __syncthreads();
     uint16_t* Dp = D + p * lo;
     if (which == 0) store_rows<T>(st, Dp, ld, int64_t(J) * T, int64_t(I) * T);
-    if (I != J && (!TWO || which == 1)) store_cols<T>(st, Dp, ld, int64_t(I) * T, int64_t(J) * T);
+    if (!TWO || which == 1) store_cols<T>(st, Dp, ld, int64_t(I) * T, int64_t(J) * T);
   }
 }
 
@@ -1320,8 +1360,10 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
     // of a 64-column block are added as (b0 + b1) + (b2 + b3).  Off-diagonal
     // tiles also emit the partials of the mirrored tile (column sums, bit for
     // bit the row sums of the transposed block, which a smaller tile size may
-    // compute as row sums), so every row of A0 gets kp / 64 partials,
-    // identical whichever tile size produced them.
+    // compute as row sums), and so do the 64-blocks below the diagonal of a
+    // diagonal tile, which a 64 tile has only as mirrors (on fp16 planes their
+    // direct sums could differ in the last bit).  So every row of A0 gets kp / 64
+    // partials, identical whichever tile size produced them.
     __syncthreads();
     float* part = reinterpret_cast<float*>(w + WL.part);
     const bool sq = (P.flags & kRowSq) != 0u;   // Schatten-4: sums of A0_ij^2
@@ -1355,7 +1397,7 @@ __global__ __launch_bounds__(Tile<T>::NTT) void k_gram_fast(const Phase P) {
     constexpr int NB64 = T / 64;
     for (int q = threadIdx.x; q < NB64 * T; q += Tile<T>::NT) {
       const int b = q / T, r = q - b * T;
-      const float* x = rs + (4 * b) * T + r;
+      const float* x = (I == J && r / 64 > b ? cs : rs) + (4 * b) * T + r;
       part[int64_t(J * NB64 + b) * kp + I * T + r] = (x[0] + x[T]) + (x[2 * T] + x[3 * T]);
       if (I != J) {
         const float* y = cs + (4 * b) * T + r;
@@ -1819,10 +1861,6 @@ __global__ __launch_bounds__(256) void k_apply_s(const Phase P) {
       uint16_t o[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) o[q] = plane_of(src[q] * (si * sv[64 + c0 + q]) * kScaleA, p);
-      uint16_t* dst = A + p * lo + int64_t(i) * WL.ldg + j0;
-      reinterpret_cast<uint4*>(dst)[0] = reinterpret_cast<const uint4*>(o)[0];
-      reinterpret_cast<uint4*>(dst)[1] = reinterpret_cast<const uint4*>(o)[1];
-      if (I == J) continue;   // uniform per block
       if (p > 0) __syncthreads();
 #pragma unroll
       for (int e = 0; e < 16; ++e) tt[r][c0 + e] = o[e];
@@ -1830,9 +1868,17 @@ __global__ __launch_bounds__(256) void k_apply_s(const Phase P) {
       uint16_t m[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) m[e] = tt[c0 + e][r];
-      uint16_t* d2 = A + p * lo + int64_t(J * 64 + r) * WL.ldg + I * 64 + c0;
-      reinterpret_cast<uint4*>(d2)[0] = reinterpret_cast<const uint4*>(m)[0];
-      reinterpret_cast<uint4*>(d2)[1] = reinterpret_cast<const uint4*>(m)[1];
+      if (I == J) {   // uniform per block; below the diagonal, the mirror (epilogue_split)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[e] = c0 + e < r ? m[e] : o[e];
+      } else {
+        uint16_t* d2 = A + p * lo + int64_t(J * 64 + r) * WL.ldg + I * 64 + c0;
+        reinterpret_cast<uint4*>(d2)[0] = reinterpret_cast<const uint4*>(m)[0];
+        reinterpret_cast<uint4*>(d2)[1] = reinterpret_cast<const uint4*>(m)[1];
+      }
+      uint16_t* dst = A + p * lo + int64_t(i) * WL.ldg + j0;
+      reinterpret_cast<uint4*>(dst)[0] = reinterpret_cast<const uint4*>(o)[0];
+      reinterpret_cast<uint4*>(dst)[1] = reinterpret_cast<const uint4*>(o)[1];
     }
     return;
   }

@@ -115,22 +115,19 @@ def test_failed_allocation_leaves_a_mixed_group_untouched(monkeypatch):
     [(70, 100), (100, 1500), (300, 310)],                        # fewer tiles than XCDs in an entry
     [(200, 260)] * 9 + [(1000, 600)] + [(130, 2000)] * 3,        # the longest products last
     [(300, 500)] * 20 + [(500, 1999)] * 5 + [(1000, 1200)] * 2,  # more than two waves of tiles
+    [(300, 400), (250, 900), (900, 1000)] + [(2048, 2048)] * 4,  # larger tiles than the single calls'
 ])
-def test_mixed_lengths_equal_single_calls(dtype, shapes):
+@pytest.mark.parametrize("precond", ["aol", "schatten4"])   # two reductions of the first Gram
+def test_mixed_lengths_equal_single_calls(dtype, shapes, precond):
     """Entries of different K in one launch: every XCD takes an eighth of each, the long ones
-    first; a tile left out or done for another matrix would show in the bits.  In fp32 the
-    bits may depend on the tile size; there the bound is twice the fp32 parity tolerance of
-    1e-4 (both calls within it of the exact result), and one wrong tile of 64 in at most
-    256 shows as 6e-2 or more."""
-    log(f"case: mixed lengths {dtype}, {len(shapes)} matrices, the last {shapes[-1]}")
+    first; a tile left out or done for another matrix would show in the bits, and so would an
+    element whose products or sums depend on the tile size."""
+    log(f"case: mixed lengths {dtype} {precond}, {len(shapes)} matrices, the last {shapes[-1]}")
     ts = [to_device(make_input(m, n, 0.8, 40 + i, dtype), dtype) for i, (m, n) in enumerate(shapes)]
     ref = [t.clone() for t in ts]
-    tm.orthogonalize_grouped(ts, 3, None, "aol")
+    tm.orthogonalize_grouped(ts, 3, None, precond)
     for t, r in zip(ts, ref):
-        tm.orthogonalize(r, 3, None, "aol")
+        tm.orthogonalize(r, 3, None, precond)
     torch.cuda.synchronize()
     for i, (t, r) in enumerate(zip(ts, ref)):
-        if dtype == "bf16":
-            assert torch.equal(t, r), i
-        else:
-            assert relF(from_device(t), from_device(r)) <= 2e-4, i
+        assert torch.equal(t, r), i
