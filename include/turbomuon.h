@@ -45,15 +45,19 @@
  * device pointers owned by the caller.  The library owns a workspace per
  * (device, stream), grown on first use with hipMalloc and kept until
  * tm_release_workspaces() or process exit; growing it synchronises `stream`.
+ * Where that much memory is not to be had, the call tries the layout with the
+ * least padding (the same results) and, in fp32, the fp32 products.
  * Calls on different streams may run concurrently; calls that overlap on the
  * same stream are ordered by the stream.  The cache is keyed by the stream
  * handle: synchronise a stream before destroying it, since a stream created
  * later may receive the same handle and reuse that workspace.
  *
  * Graph capture.  A call on a stream whose workspace is already large enough
- * (an earlier call of the same or larger shapes on that stream) allocates
- * nothing and synchronises nothing, so it can be captured into a HIP graph;
- * the captured kernels keep that workspace's address.  A call under capture
+ * (an earlier call of the same or larger shapes and the same type on that
+ * stream, whatever its iters, coeffs and precond; calls of the single-launch
+ * kernel need no workspace and reserve none) allocates nothing and synchronises
+ * nothing, so it can be captured into a HIP graph; the captured kernels keep
+ * that workspace's address.  A call under capture
  * whose workspace is too small returns TM_ERR_UNSUPPORTED (nothing can be
  * allocated during capture).  A workspace once used under capture is never
  * freed or reused in place by a larger call: a later, larger eager call on the

@@ -45,7 +45,8 @@ constexpr float kA = 3.4445f, kB = -4.7750f, kC = 2.0315f;
 struct Workspace {
   void* ptr = nullptr;
   size_t bytes = 0;
-  bool captured = false;   // used by a call under graph capture: never freed or reused in place
+  size_t refused = SIZE_MAX;   // smallest reserve (beyond what a call needed) that could not be had
+  bool captured = false;       // used by a call under graph capture: never freed or reused in place
 };
 
 std::mutex g_mu;
@@ -113,20 +114,36 @@ tm_status check_device(int* dev) {
   return TM_OK;
 }
 
-// Grow the (device, stream) buffer of a cache to at least `bytes`.  Under
-// graph capture nothing may be allocated, freed or synchronised: the buffer
-// must already be large enough, and it is then marked as captured.  A captured
-// buffer keeps its address for the graphs that hold it: a later, larger eager
-// call on that stream handle gets a new buffer, and the old one is retired
-// (freed by tm_release_workspaces only).
-tm_status get_workspace(int dev, hipStream_t st, size_t bytes, char** out, WsCache& cache = g_ws) {
-  Workspace& w = cache[{dev, st}];
+bool capturing(hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
     (void)hipGetLastError();
-    cap = hipStreamCaptureStatusNone;
+    return false;
   }
-  if (cap != hipStreamCaptureStatusNone) {
+  return cap != hipStreamCaptureStatusNone;
+}
+
+// Device memory of a workspace.  TM_TEST_FAIL_ALLOC in the environment refuses
+// requests of at least that many bytes.
+void* device_alloc(size_t bytes) {
+  const char* refuse = std::getenv("TM_TEST_FAIL_ALLOC");
+  if (refuse != nullptr && bytes >= std::strtoull(refuse, nullptr, 10)) return nullptr;
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+// Grow the (device, stream) buffer of a cache to at least `bytes`, to `reserve`
+// (>= bytes) where that can be had.  Under graph capture (`cap`) nothing may be
+// allocated, freed or synchronised: the buffer must already be large enough, and
+// it is then marked as captured.  A captured buffer keeps its address for the
+// graphs that hold it: a later, larger eager call on that stream handle gets a new
+// buffer, and the old one is retired (freed by tm_release_workspaces only).
+tm_status get_workspace(int dev, hipStream_t st, size_t bytes, size_t reserve, bool cap, char** out,
+                        WsCache& cache = g_ws) {
+  Workspace& w = cache[{dev, st}];
+  if (cap) {
     if (w.bytes < bytes)
       return fail(TM_ERR_UNSUPPORTED,
                   "the stream's workspace holds " + std::to_string(w.bytes) + " bytes, the call "
@@ -136,29 +153,27 @@ tm_status get_workspace(int dev, hipStream_t st, size_t bytes, char** out, WsCac
     *out = static_cast<char*>(w.ptr);
     return TM_OK;
   }
-  if (w.bytes < bytes) {
+  if (w.bytes < bytes || (w.bytes < reserve && reserve < w.refused)) {
     if (w.ptr && w.captured) {
       g_retired.push_back(w.ptr);
-      w.ptr = nullptr;
-      w.bytes = 0;
-      w.captured = false;
     } else if (w.ptr) {
       hipError_t e = hipStreamSynchronize(st);
       if (e != hipSuccess)
         return fail(TM_ERR_HIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
       (void)hipFree(w.ptr);
-      w.ptr = nullptr;
-      w.bytes = 0;
     }
-    void* p = nullptr;
-    if (std::getenv("TM_TEST_FAIL_ALLOC") != nullptr ||
-        hipMalloc(&p, bytes) != hipSuccess || p == nullptr) {
-      (void)hipGetLastError();
-      return fail(TM_ERR_NO_MEMORY, "workspace allocation of " + std::to_string(bytes) +
-                                        " bytes failed");
+    w = Workspace{nullptr, 0, w.refused, false};
+    size_t size = std::max(bytes, reserve);
+    void* p = device_alloc(size);
+    if (p == nullptr && size > bytes) {
+      w.refused = std::min(w.refused, size);   // not tried again by every later call
+      size = bytes;
+      p = device_alloc(size);
     }
+    if (p == nullptr)
+      return fail(TM_ERR_NO_MEMORY, "workspace allocation of " + std::to_string(bytes) + " bytes failed");
     w.ptr = p;
-    w.bytes = bytes;
+    w.bytes = size;
   }
   *out = static_cast<char*>(w.ptr);
   return TM_OK;
@@ -300,12 +315,15 @@ uint64_t laid_bytes(std::vector<Item> shapes, int cfg, int esz) {
 // in view: a bf16 call that fits it on a smaller tile takes that one, whichever
 // entry point it came by (equal launches, and tm_workspace_bytes tells which
 // calls fit).  4 x 1044 x 1480: 67.8 MB on 128 tiles, 61.9 on 64; near the
-// limit the padding of the larger tile is what decides.
-int layout_cfg(const std::vector<Item>& shapes, int esz) {
-  constexpr uint64_t kLimit = TM_NOALLOC_SCRATCH_BYTES;
+// limit the padding of the larger tile is what decides.  With `limit`, the bytes
+// that a call under capture or short of memory can have, also no tile beyond it
+// but the smallest (whose layout is the smallest too): the results do not depend
+// on the tile.
+int layout_cfg(const std::vector<Item>& shapes, int esz, uint64_t limit = UINT64_MAX) {
+  constexpr uint64_t kScratch = TM_NOALLOC_SCRATCH_BYTES;
   int cfg = choose_tile_cfg(shapes, esz == 4 ? 3 : 1);
-  if (esz == 2 && laid_bytes(shapes, tmk::kNumCfg - 1, esz) <= kLimit)
-    while (laid_bytes(shapes, cfg, esz) > kLimit) ++cfg;
+  if (esz == 2 && laid_bytes(shapes, tmk::kNumCfg - 1, esz) <= kScratch) limit = std::min(limit, kScratch);
+  while (limit != UINT64_MAX && cfg < tmk::kNumCfg - 1 && laid_bytes(shapes, cfg, esz) > limit) ++cfg;
   return cfg;
 }
 
@@ -967,6 +985,18 @@ tm_status plan_f32(const Plan& pl, int iters, const float* coeffs, int precond) 
   return s;
 }
 
+// Workspace of a call in the form that needs the most, each on its smallest
+// layout (fp32 on planes needs more than on the fp32 kernels).
+uint64_t smallest_bytes(std::vector<Item> items, int esz) {
+  uint64_t total = 0;
+  for (Item& it : items) {
+    if (esz == 2 || split_rule(it)) tmk::tiled_dims(it.k, it.N, tmk::kMinTile, &it.kp, &it.Np);
+    else tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
+    total += item_ws(it, esz);
+  }
+  return total;
+}
+
 // Plan and enqueue one call (g_mu held, device checked).  With ext_ws the
 // call runs in that caller-provided device buffer of ext_bytes bytes (the
 // allocation-free entry point) instead of the per-stream workspace cache, and
@@ -996,12 +1026,12 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) {
       return double(x.k) * x.k * x.N * x.count > double(y.k) * y.k * y.N * y.count;
     });
-  // parts of the call that run one after the other: bf16 is one, fp32 the
-  // matrices on fp16 planes and the others
-  std::vector<Item> part[2];
-  Plan pl[2];
-  uint64_t total = 0;
+  const bool cap = ext_ws == nullptr && capturing(st);
   const bool half = half_ok(iters, coeffs, precond);
+  // What a call of these shapes needs in any form (they differ by iters, coefficients
+  // and precond), on the smallest tile: reserved by every call, so that one call serves
+  // the capture of any other of the same or smaller shapes.
+  const uint64_t every_form = smallest_bytes(items, esz);
   // A call whose matrices are pairs but for some in the fused kernel's range runs
   // those there, in one launch: step by step on tiles they would add about eight
   // launches to the pairs' chain.  (Bit for bit the same results.)
@@ -1012,36 +1042,52 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     if (!pairs.empty() && std::all_of(small.begin(), small.end(), small_eligible)) items = pairs;
     else small.clear();
   }
-  const bool planes = esz == 4 && iters > 0 && half_ok(iters, coeffs, precond, 16.0);
-  for (const Item& it : items) part[esz == 2 || (planes && split_rule(it)) ? 0 : 1].push_back(it);
-  for (int p = 0; p < 2; ++p) {
-    if (part[p].empty()) continue;
-    pl[p].items = &part[p];
-    pl[p].esz = esz;
-    pl[p].st = st;
-    pl[p].split = p == 0 && esz == 4;
-    if (p == 0) {
-      for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
-      pl[p].tcfg = layout_cfg(shapes_of(part[p]), esz);
-      for (Item& it : part[p]) {
-        tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);
-        const int updates = it.pair ? (iters + 1) / 2 : iters;
-        // A wide matrix that needs no padding is read in place by the first
-        // update; a single update would read and write the caller's buffer in
-        // the same launch, so it keeps the copy.
-        it.direct = esz == 2 && !it.tall && it.kp == it.k && it.Np == it.N && updates != 1 &&
-                    (reinterpret_cast<uintptr_t>(it.x) & 15u) == 0u;
+  // parts of the call that run one after the other: bf16 is one, fp32 the
+  // matrices on fp16 planes (`planes`) and the others
+  std::vector<Item> part[2];
+  Plan pl[2];
+  auto lay_out = [&](bool planes, uint64_t limit) {
+    uint64_t total = 0;
+    for (int p = 0; p < 2; ++p) {
+      part[p].clear();
+      pl[p] = Plan();
+    }
+    for (const Item& it : items) part[esz == 2 || (planes && split_rule(it)) ? 0 : 1].push_back(it);
+    uint64_t rest = 0;   // the other part's layout is what it is
+    for (Item& it : part[1]) {
+      tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
+      rest += item_ws(it, esz);
+    }
+    for (int p = 0; p < 2; ++p) {
+      if (part[p].empty()) continue;
+      pl[p].items = &part[p];
+      pl[p].esz = esz;
+      pl[p].st = st;
+      pl[p].split = p == 0 && esz == 4;
+      if (p == 0) {
+        for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
+        pl[p].tcfg = layout_cfg(shapes_of(part[p]), esz, limit == UINT64_MAX ? limit : limit - std::min(limit, rest));
+        for (Item& it : part[p]) {
+          tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);
+          const int updates = it.pair ? (iters + 1) / 2 : iters;
+          // A wide matrix that needs no padding is read in place by the first
+          // update; a single update would read and write the caller's buffer in
+          // the same launch, so it keeps the copy.
+          it.direct = esz == 2 && !it.tall && it.kp == it.k && it.Np == it.N && updates != 1 &&
+                      (reinterpret_cast<uintptr_t>(it.x) & 15u) == 0u;
+        }
       }
-    } else {
-      for (Item& it : part[p]) tmk::generic_dims(it.k, it.N, &it.kp, &it.Np);
+      pl[p].shapes = shapes_of(part[p]);
+      std::memset(pl[p].tile_of, -1, sizeof(pl[p].tile_of));
+      for (const Item& it : part[p]) {
+        pl[p].ws_off.push_back(total);
+        total += item_ws(it, esz);
+      }
     }
-    pl[p].shapes = shapes_of(part[p]);
-    std::memset(pl[p].tile_of, -1, sizeof(pl[p].tile_of));
-    for (const Item& it : part[p]) {
-      pl[p].ws_off.push_back(total);
-      total += item_ws(it, esz);
-    }
-  }
+    return total;
+  };
+  const bool planes = esz == 4 && iters > 0 && half_ok(iters, coeffs, precond, 16.0);
+  uint64_t total = lay_out(planes, cap ? g_ws[{dev, st}].bytes : UINT64_MAX);
   if (total >= (uint64_t(1) << 40))   // entries hold offsets in 256-byte units
     return fail(TM_ERR_UNSUPPORTED, "workspace of more than 1 TB");
   char* ws = ext_ws;
@@ -1051,8 +1097,15 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
                                           " bytes of scratch; the static scratch holds " +
                                           std::to_string(ext_bytes));
   } else {
-    s = get_workspace(dev, st, size_t(total), &ws);
+    s = get_workspace(dev, st, size_t(total), size_t(every_form), cap, &ws);
+    // short of memory: the layout with the least padding, then (fp32) the kernels
+    // that need none
+    for (int least = 0; least < (planes ? 2 : 1) && s == TM_ERR_NO_MEMORY; ++least) {
+      total = lay_out(planes && least == 0, 0);
+      s = get_workspace(dev, st, size_t(total), size_t(total), cap, &ws);
+    }
     if (s != TM_OK) return s;
+    g_last_error.clear();
   }
   // nothing is enqueued before this point, where the call can still fail
   if (!small.empty()) {
@@ -1274,7 +1327,7 @@ tm_status tm_muon_step_grouped(float* const* W, const float* const* G, float* co
   uint64_t ubytes = 0;
   for (int64_t g = 0; g < count; ++g) ubytes += tmk::align256(uint64_t(m[g]) * uint64_t(n[g]) * 2u);
   char* ubase = nullptr;
-  s = get_workspace(dev, st, size_t(ubytes), &ubase, g_ws_u);
+  s = get_workspace(dev, st, size_t(ubytes), size_t(ubytes), capturing(st), &ubase, g_ws_u);
   if (s != TM_OK) return s;
   std::vector<tmk::OptEntry> ents(static_cast<size_t>(count));
   std::vector<Item> items;

@@ -37,3 +37,26 @@ def test_failed_allocation_reports_no_memory_and_recovers(monkeypatch):
     tm.orthogonalize(x, 4, None, "aol")
     torch.cuda.synchronize()
     assert torch.equal(x, ref)
+
+
+def test_short_of_memory_takes_a_smaller_workspace(monkeypatch):
+    """Refused allocations from the size of the preferred layout on: the call runs on the
+    layout with the least padding (same bits), and fp32 also on the fp32 kernels, which need
+    less than the padded planes."""
+    log("case: workspace allocations refused from a size on")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    for dtype, shape, refused, bound in ((torch.bfloat16, (1, 3365, 6105), 185 * 10 ** 6, 0.0),
+                                         (torch.float32, (40, 65, 65), 10 * 10 ** 6, 2e-4)):
+        # 181 MB on tiles of 64 and 128, 192 MB on 256; 13 MB as planes, 4 MB in fp32
+        x = torch.randn(shape, generator=g, device="cuda").to(dtype)
+        ref = x.clone()
+        tm.orthogonalize(ref, 4, None, "aol")
+        torch.cuda.synchronize()
+        tm.release_workspaces()
+        monkeypatch.setenv("TM_TEST_FAIL_ALLOC", str(refused))
+        tm.orthogonalize(x, 4, None, "aol")
+        torch.cuda.synchronize()
+        monkeypatch.delenv("TM_TEST_FAIL_ALLOC")
+        tm.release_workspaces()
+        assert float((x.double() - ref.double()).norm() / ref.double().norm()) <= bound

@@ -156,3 +156,52 @@ def test_capture_with_too_small_a_workspace_is_refused():
     torch.cuda.synchronize()
     assert torch.equal(x, keep)
     del graph
+
+
+def _shape_inputs(shapes, dtype):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    # sigma_max about 1: unscaled calls stay finite
+    return [(torch.randn(s, generator=g, device="cuda") / (s[0] ** 0.5 + s[1] ** 0.5)).to(dtype) for s in shapes]
+
+
+# (type, shapes of the earlier call, its iters and precond, shapes captured, their iters and precond)
+FORMS = [
+    ("f32", [(1000, 1000)], 0, "aol", None, 4, "aol"),          # fp32 kernels, then fp16 planes
+    ("f32", [(65, 300)] * 3, 2, "none", None, 4, "frobenius"),
+    ("bf16", [(3365, 6105)], 4, "none", None, 4, "aol"),        # step by step, then in pairs
+    ("bf16", [(768, 3072), (64, 576)], 4, "aol", None, 4, "none"),   # pairs and fused, then all step by step
+    ("f32", [(1100, 1300), (300, 800)], 4, "aol", [(1026, 1290), (260, 700)], 4, "aol"),
+    ("bf16", [(1500, 1700)] * 9, 4, "aol", [(1281, 1537)] * 8, 4, "aol"),
+]
+
+
+@pytest.mark.parametrize("dtype,warm,w_iters,w_precond,shapes,iters,precond", FORMS)
+def test_one_call_serves_the_capture_of_every_form(dtype, warm, w_iters, w_precond, shapes, iters, precond):
+    """An earlier call of the same or larger shapes is enough for a capture, whatever form its
+    iterations, coefficients and scale gave it; the replays have the bits of an eager call."""
+    log(f"case: {dtype} {warm} {w_precond} t={w_iters}, then captured {shapes or warm} {precond} t={iters}")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    tm.release_workspaces()
+    side = torch.cuda.Stream()
+    first = _shape_inputs(warm, dt)
+    X0 = _shape_inputs(shapes or warm, dt)
+    ref = [x.clone() for x in X0]
+    tm.orthogonalize_grouped(ref, iters, None, precond)      # another stream, another workspace
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        tm.orthogonalize_grouped(first, w_iters, None, w_precond)
+    side.synchronize()
+    buf = [x.clone() for x in X0]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        tm.orthogonalize_grouped(buf, iters, None, precond)
+    for _ in range(3):
+        for b, x in zip(buf, X0):
+            b.copy_(x)
+        _busy_work()
+        graph.replay()
+        torch.cuda.synchronize()
+        for b, e in zip(buf, ref):
+            assert torch.equal(b, e)
