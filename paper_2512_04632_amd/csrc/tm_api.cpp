@@ -339,6 +339,7 @@ struct Plan {
   // tile and classes (-1: none yet)
   mutable int tile_of[tmk::kNumKinds][2][3];
   bool split = false;             // fp32 on fp16 planes (tm_fast.hip's kernels)
+  float raise = 0.f;              // size that small rows are worked on at (raise_to); 0: their own
   bool timed = true;              // the timing hooks may bracket this call's launches
 };
 
@@ -693,6 +694,8 @@ tm_status plan_small(const Plan& pl, int iters, const float* coeffs, int precond
   return TM_OK;
 }
 
+uint32_t raise_flag(const Plan& pl) { return pl.raise > 0.f ? tmk::kRaise : 0u; }
+
 // Scale vector s from the first Gram (its flags carry the row partials):
 // AOL (Algorithm 2, second line) s_i = 1 / sqrt(row sum of |A0|); Schatten-4
 // the uniform ||A0||_F^(-1/2), summed from the squares' row partials.  `part`
@@ -702,7 +705,7 @@ tm_status gram_scale(const Plan& pl, int precond, int part) {
     return launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, 0u, part);
   tm_status s = launch(pl, tmk::kKindFrob, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFromPart, part);
   if (s == TM_OK)
-    s = launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob | tmk::kS4, 0);
+    s = launch(pl, tmk::kKindAolVector, 0, 0, 0, pl.raise, 0.f, 0.f, tmk::kFrob | tmk::kS4 | raise_flag(pl), 0);
   return s;
 }
 
@@ -717,7 +720,7 @@ uint32_t first_gram_flags(int precond) {
 // Algorithm 1 the trace of the first Gram, ||X0||_F^2).
 tm_status first_scale(const Plan& pl, int precond, int part) {
   if (precond == TM_PRECOND_FROBENIUS)
-    return launch(pl, tmk::kKindAolVector, 0, 0, 0, 0.f, 0.f, 0.f, tmk::kFrob | tmk::kTrace, 0);
+    return launch(pl, tmk::kKindAolVector, 0, 0, 0, pl.raise, 0.f, 0.f, tmk::kFrob | tmk::kTrace | raise_flag(pl), 0);
   return gram_scale(pl, precond, part);
 }
 
@@ -729,13 +732,15 @@ Triple triple(const float* coeffs, int it) {
   return coeffs ? Triple{coeffs[3 * it], coeffs[3 * it + 1], coeffs[3 * it + 2]} : Triple{kA, kB, kC};
 }
 
-// Whether a bf16 call may take iterations two at a time (pair_rule), with the
-// k x k matrices in fp16.  After any scaling sigma_max(X1) <= 1, so every A, T = B~ A and B~
-// of the call is bounded by its coefficients: with x the largest sigma^2,
-// |B~| <= max |q| over [0, x], q(x) = a + b x + c x^2, and the next x is the
-// largest x q(x)^2.  The call qualifies while A and T stay below 8 (32768 as
-// stored, half of fp16's largest) and B~ below 32 (32768).
-bool half_ok(int iters, const float* coeffs, int precond, double top_b = 32.0) {
+// Whether a call's k x k matrices stay within fp16's range (pairs, planes).  After
+// any scaling sigma_max(X1) <= 1, so every A, T = B~ A and B~ of the call is
+// bounded by its coefficients: with x the largest sigma^2, |B~| <= max |q| over
+// [0, x], q(x) = a + b x + c x^2, and the next x is the largest x q(x)^2.  The call
+// qualifies while A and T stay below 8 (32768 as stored, half of fp16's largest)
+// and B~ below 32 (32768).  *growth: the most that all iterations together
+// multiply a row by, the product of max |q| (at least 1 each).
+bool half_ok(int iters, const float* coeffs, int precond, double top_b, double* growth) {
+  *growth = 1.0;
   if (precond == TM_PRECOND_NONE) return false;
   double x = 1.02;   // the scale's own rounding
   for (int it = 0; it < iters; ++it) {
@@ -745,6 +750,7 @@ bool half_ok(int iters, const float* coeffs, int precond, double top_b = 32.0) {
     double top = std::max(std::fabs(a), std::fabs(q(x)));
     if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < x) top = std::max(top, std::fabs(q(-b / (2 * c))));
     if (!(x <= 8.0 && top <= top_b && x * top <= 8.0)) return false;
+    *growth *= std::max(top, 1.0);
     double nx = 0.0;
     constexpr int S = 128;
     for (int i = 1; i <= S; ++i) {
@@ -754,6 +760,24 @@ bool half_ok(int iters, const float* coeffs, int precond, double top_b = 32.0) {
     x = 1.02 * nx;   // between the samples, and the rounding of the products
   }
   return x <= 8.0;
+}
+
+// Small rows under a uniform scale (Frobenius, Schatten-4), which AOL brings to
+// like sizes: beside rows of size 1 their entries of A, B~ and Y fall below what
+// fp16 (times kScaleA and so on) or two fp16 planes hold, so that a row of 2^-30 came
+// out 100% (pairs) and 6e-3 (planes, 1024 x 2048) of itself off, and one of 2^-50 as
+// zero.  They are therefore worked on at a size of `raise`, 2^-18 or so: s_i is s
+// times a power of two, and the last update takes the factor out again (both
+// exact).  To the other rows and to its own q(Y^T Y) such a row is the square of
+// raise times the growth: 96 x 500 to 1024 x 2048, rows of 2^-10 to 2^-60, five
+// iterations of a = 3.44 (growth 2^9): small rows are 4e-7 off (planes) and 6e-3
+// (pairs), as the others are.  2^-14 is too large (1e-5), 2^-22 begins to show the
+// formats' resolution (2e-6): from a growth of 2^14 on (8 iterations of the default
+// coefficients) neither fits, and uniform scales keep the fp32 products and the
+// step-by-step form.  0: no raise there.
+float raise_to(double growth) {
+  const int e = -8 - int(std::ceil(std::log2(growth)));
+  return e < -22 ? 0.f : std::ldexp(1.f, std::min(e, -18));
 }
 
 // Two iterations per update (class 1).  Iterations k, k + 1 as printed take two
@@ -797,7 +821,7 @@ bool split_rule(const Item& it) { return it.k >= 64; }
 // `pair`), n = 1 or 2, from A in kBufA; `scaled`: the update's factor times
 // diag(s).
 void block_steps(std::vector<Step>& out, bool pair, bool split, int it, int n, const float* coeffs, bool scaled,
-                 int src, int dst) {
+                 int src, int dst, uint32_t update_flags) {
   const float sa = pair || split ? tmk::kScaleA : 1.f, sb = pair || split ? tmk::kScaleB : 1.f;
   auto product = [&](int l, int r, int m, int o, float al, float be, float ga, bool factor) {
     Step s{tmk::kKindPoly, 0u};
@@ -813,7 +837,7 @@ void block_steps(std::vector<Step>& out, bool pair, bool split, int it, int n, c
     const float f = factor && !split ? 1.f : sb;
     product(tmk::kBufA, tmk::kBufA, tmk::kBufA, o, t.c * (f / (sa * sa)), t.b * (f / sa), t.a * f, factor);
   };
-  Step u{tmk::kKindUpdate, 0u};
+  Step u{tmk::kKindUpdate, update_flags};
   u.src = src;
   u.dst = dst;
   if (n == 1) {
@@ -920,7 +944,7 @@ tm_status plan_tiled(const Plan& pl, int iters, const float* coeffs, int precond
         g.src = src;
         seq[cls].push_back(g);
       }
-      block_steps(seq[cls], cls == 1, pl.split, it, n, coeffs, it == 0 && scaled, src, dst);
+      block_steps(seq[cls], cls == 1, pl.split, it, n, coeffs, it == 0 && scaled, src, dst, raise_flag(pl));
       src = dst;
       it += n;
     }
@@ -1027,7 +1051,12 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
       return double(x.k) * x.k * x.N * x.count > double(y.k) * y.k * y.N * y.count;
     });
   const bool cap = ext_ws == nullptr && capturing(st);
-  const bool half = half_ok(iters, coeffs, precond);
+  const bool uniform = precond != TM_PRECOND_AOL;
+  double growth;
+  const bool half = half_ok(iters, coeffs, precond, esz == 2 ? 32.0 : 16.0, &growth);
+  const float raise = half && uniform ? raise_to(growth) : 0.f;
+  // pairs (bf16), planes (fp32)
+  const bool fp16 = half && (!uniform || esz == 2 || raise > 0.f);
   // What a call of these shapes needs in any form (they differ by iters, coefficients
   // and precond), on the smallest tile: reserved by every call, so that one call serves
   // the capture of any other of the same or smaller shapes.
@@ -1036,7 +1065,7 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   // those there, in one launch: step by step on tiles they would add about eight
   // launches to the pairs' chain.  (Bit for bit the same results.)
   std::vector<Item> small;
-  if (esz == 2 && iters >= 2 && half && std::getenv("TM_DISABLE_FUSED") == nullptr) {
+  if (esz == 2 && iters >= 2 && fp16 && std::getenv("TM_DISABLE_FUSED") == nullptr) {
     std::vector<Item> pairs;
     for (const Item& it : items) (pair_rule(it) ? pairs : small).push_back(it);
     if (!pairs.empty() && std::all_of(small.begin(), small.end(), small_eligible)) items = pairs;
@@ -1064,8 +1093,9 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
       pl[p].esz = esz;
       pl[p].st = st;
       pl[p].split = p == 0 && esz == 4;
+      pl[p].raise = pl[p].split ? raise : 0.f;
       if (p == 0) {
-        for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && half && pair_rule(it);
+        for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && fp16 && pair_rule(it);
         pl[p].tcfg = layout_cfg(shapes_of(part[p]), esz, limit == UINT64_MAX ? limit : limit - std::min(limit, rest));
         for (Item& it : part[p]) {
           tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);
@@ -1086,7 +1116,7 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
     }
     return total;
   };
-  const bool planes = esz == 4 && iters > 0 && half_ok(iters, coeffs, precond, 16.0);
+  const bool planes = esz == 4 && iters > 0 && fp16;
   uint64_t total = lay_out(planes, cap ? g_ws[{dev, st}].bytes : UINT64_MAX);
   if (total >= (uint64_t(1) << 40))   // entries hold offsets in 256-byte units
     return fail(TM_ERR_UNSUPPORTED, "workspace of more than 1 TB");

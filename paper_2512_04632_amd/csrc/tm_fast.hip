@@ -1538,6 +1538,13 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
   // interleave, as the operand reads of the row-major Y stage assign them)
   const int lane = threadIdx.x & 63;
   const int wm = wave_m(Tile<T>::WGN), wn = wave_n(Tile<T>::WGN);
+  // rows scaled by more than the uniform s (a power of two more): taken out of the result
+  const bool raised = (P.flags & kRaise) && dst == kSlotFinal && (kSplit || (E.flags & kPair));
+  const float* sv = reinterpret_cast<const float*>(w + WL.s) + I * T;
+  auto lower = [=](int r) __attribute__((always_inline)) {
+    const float si = sv[r], su = reinterpret_cast<const float*>(w + WL.fpart)[kFrobBlocks];
+    return si > 0.f ? su / si : 1.f;
+  };
   if constexpr (kSplit) {
     if (dst != kSlotFinal) {
       uint16_t* D = wbuf(P, E, L.mat, dst);
@@ -1567,9 +1574,10 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
     float* X = reinterpret_cast<float*>(user_of(P, E, L.mat));
     const bool tall = (E.flags & kTall) != 0u;
     const bool vec = (N % 4) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0u;
-    constexpr float f = 1.f / (kScaleB * kScaleY);
 #pragma unroll
-    for (int fm = 0; fm < FM; ++fm)
+    for (int fm = 0; fm < FM; ++fm) {
+      float f = 1.f / (kScaleB * kScaleY);
+      if (raised) f *= lower(wm * Tile<T>::TWM + fm * 16 + (lane & 15));
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn) {
         const int i = I * T + wm * Tile<T>::TWM + fm * 16 + (lane & 15);
@@ -1585,6 +1593,7 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
     return;
   }
 #pragma unroll
@@ -1599,6 +1608,16 @@ __global__ __launch_bounds__(Tile<T>::NT) void k_update_fast(const Phase P) {
       *reinterpret_cast<uint2*>(smem + i * Stage<T>::RS + l0 * 2) = *reinterpret_cast<const uint2*>(out);
     }
   __syncthreads();
+  if (raised) {   // in the stage, which leaves the products' registers alone: a power of two is exact there too
+    for (int r = int(threadIdx.x); r < T; r += Tile<T>::NT) {
+      const float f = lower(r);
+      if (f == 1.f) continue;
+      uint16_t* row = reinterpret_cast<uint16_t*>(smem + r * Stage<T>::RS);
+#pragma unroll 1
+      for (int c = 0; c < T; ++c) row[c] = f2bf(bf2f(row[c]) * f);
+    }
+    __syncthreads();
+  }
   if (dst != kSlotFinal)
     store_rows<T>(smem, wbuf(P, E, L.mat, dst), ldy, int64_t(I) * T, int64_t(Lb) * T);
   else if ((E.flags & kTall) == 0u)

@@ -57,6 +57,8 @@ constexpr uint32_t kTail = 128u;  // matrix-core kernels: blocks are 2 x 2 sub-t
 constexpr uint32_t kTail4 = 512u; // with kTail (update only): 4 x 4 sub-tiles of a quarter size
 constexpr uint32_t kBySlice = 1024u;  // matrix-core kernels: XCD x runs an eighth of every entry's tiles
 constexpr uint32_t kTrace = 4096u;   // with kFrob: s = (trace of the first Gram)^(-1/2)
+constexpr uint32_t kRaise = 2048u;   // scale vector: small rows get more than the uniform scale (Phase::a);
+                                     // last update: takes it out again
 constexpr uint32_t kFuseS = 256u; // bf16 rescale of A0: the AOL vector is summed in the same
                                   // kernel from the Gram's row partials (aux columns each)
 
@@ -105,7 +107,8 @@ struct Ops {
   TM_HD int out() const { return int(v >> 12 & 3u); }
 };
 
-constexpr int kFrobBlocks = 32;   // partial sums of squares per matrix
+constexpr int kFrobBlocks = 32;   // partial sums of squares per matrix (with kRaise followed by
+                                  // the uniform scale)
 constexpr int kMinTile = 64;      // smallest Gram tile: bounds the row-sum partial count
 
 struct Entry {
@@ -268,7 +271,7 @@ TM_HD WsLayout ws_layout(uint32_t kp, uint32_t Np, uint32_t esz) {
   L.s = L.a32 + align256(uint64_t(kp) * kp * 4u);
   L.part = L.s + align256(uint64_t(kp) * 4u);
   L.fpart = L.part + align256(uint64_t(cdiv(kp, kMinTile)) * kp * 4u);
-  L.total = L.fpart + align256(uint64_t(kFrobBlocks) * 4u);
+  L.total = L.fpart + align256(uint64_t(kFrobBlocks + 1) * 4u);
   return L;
 }
 

@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256) void k_frob_partial(const Phase P) {
 // order.  Fixed summation order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_aol_vector(const Phase P) {
-  __shared__ float red[4];
+  __shared__ float red[4], su;
   const Loc L = locate(P, blockIdx.x);
   const Entry& E = L.E;
   const int k = int(E.k), kp = int(E.kp);
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(256) void k_aol_vector(const Phase P) {
     for (int q = int(threadIdx.x); q < k; q += 256) tr += A0[int64_t(q) * (kp + 1)];
     tr = block_sum_256(tr, red);
   }
-  if (i >= kp) return;
+  const bool raise = (P.flags & kRaise) != 0u && (sizeof(T) == 4 || (E.flags & kPair) != 0u);
   float r = 0.f;
   if (i < k) {
     if (P.flags & kTrace) {
@@ -699,7 +699,33 @@ __global__ __launch_bounds__(256) void k_aol_vector(const Phase P) {
     }
   }
   const float q = (P.flags & kS4) ? sqrtf(r) : r;         // Schatten-4: ||A0||_F
-  s[i] = r >= 1.17549435e-38f ? 1.0f / sqrtf(q) : 0.f;   // padding rows: 0
+  const float v = r >= 1.17549435e-38f ? 1.0f / sqrtf(q) : 0.f;   // padding rows: 0
+  if (!raise) {
+    if (i < kp) s[i] = v;
+    return;
+  }
+  // Rows of size u = s sqrt(A0_ii) below P.a: s_i = 2^e s with 2^e u at most P.a, and all
+  // of them together no larger (their number under the root).  Every thread
+  // of the block with i < k holds the same v; the sum is over all rows.
+  if (threadIdx.x == 0) su = v;   // its row is one of the matrix (i < k), or none of the block's is
+  __syncthreads();
+  const float lim = P.a / su;
+  const float* A0 = reinterpret_cast<const float*>(w + WL.a32);
+  float few = 0.f;
+#pragma unroll 8
+  for (int j = int(threadIdx.x); j < k; j += 256) {
+    const float d = A0[int64_t(j) * (kp + 1)];
+    few += d > 0.f && d < lim * lim ? 1.f : 0.f;
+  }
+  few = block_sum_256(few, red);
+  if (i >= kp) return;
+  float f = 1.f;
+  if (i < k && few > 0.f) {
+    const float u = v * sqrtf(A0[int64_t(i) * (kp + 1)]), up = P.a / sqrtf(few) / u;
+    if (u > 0.f && up > 1.f && up < 3e38f) f = __uint_as_float(__float_as_uint(up) & 0x7f800000u);   // 2^e <= up
+  }
+  s[i] = v * f;
+  if (i == 0) reinterpret_cast<float*>(w + WL.fpart)[kFrobBlocks] = v;
 }
 
 // X1 = diag(s) X0 in place on the user matrix (rows of the wide view).

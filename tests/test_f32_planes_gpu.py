@@ -39,18 +39,35 @@ def test_planes_match_oracle(k, N, precond, iters, coeffs):
 
 
 @pytest.mark.parametrize("tall", [False, True])
-@pytest.mark.parametrize("precond,decades", [("aol", 6), ("frobenius", 3)])
+@pytest.mark.parametrize("precond,decades", [("aol", 6), ("frobenius", 3), ("frobenius", 7), ("schatten4", 7)])
 def test_small_rows_keep_their_bits(tall, precond, decades):
     """Rows 10^-decades .. 10^decades of the others' size: the planes of X are scaled row by
-    row, and a lo plane underflows only after its hi plane, so the smallest rows of X1 (AOL:
-    10^-decades, Frobenius: 10^-2 decades) come out with the accuracy of the largest."""
-    log(f"case: row scales far apart, {precond} tall={tall}")
+    row and a lo plane underflows only after its hi plane, and under a uniform scale rows below
+    2^-18 are worked on at that size, so the smallest rows of X1 (AOL: 10^-decades, the uniform
+    scales: 10^-2 decades) come out with the accuracy of the largest."""
+    log(f"case: row scales far apart, {precond} {decades} tall={tall}")
     X = make_input(96, 500, 0.8, 3, "f32")
     X = (X * np.logspace(-decades, decades, 96)[:, None]).astype(np.float32).astype(np.float64)
     R = O.orthogonalize(X, 4, None, precond)
     G = one(X.T if tall else X, 4, precond)
     G = G.T if tall else G
     for i in range(96):
+        assert np.linalg.norm(G[i] - R[i]) <= TOL * np.linalg.norm(R[i]), i
+
+
+@pytest.mark.parametrize("precond,iters", [("frobenius", 1), ("frobenius", 5), ("schatten4", 4)])
+@pytest.mark.parametrize("k,N", [(64, 64), (300, 1000), (1000, 1100)])
+def test_few_small_rows_under_a_uniform_scale(k, N, precond, iters):
+    """Rows far below the others, in several blocks of the scale vector and at the tiles' edges."""
+    log(f"case: few small rows, {k}x{N} {precond} t={iters}")
+    X = make_input(k, N, 0.8, 9, "f32")
+    small = sorted({0, 31, 63, k // 2, k - 1})
+    X[small] *= np.array([2.0 ** -e for e in (20, 30, 40, 24, 50)])[: len(small), None]
+    X[small[1]] *= 2.0 ** -10
+    R = O.orthogonalize(X, iters, None, precond)
+    G = one(X, iters, precond)
+    assert relF(G, R) <= TOL
+    for i in small:
         assert np.linalg.norm(G[i] - R[i]) <= TOL * np.linalg.norm(R[i]), i
 
 
