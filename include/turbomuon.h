@@ -24,12 +24,18 @@
  * AOL row sums are taken from the fp32 Gram accumulators.  Where the long side
  * is much the longer (max(m, n) at least 9 min(m, n) from min(m, n) = 256 on,
  * 4 from 512, 2 from 1280 and 1.5 from 3072 on), two iterations share one Gram
- * and one update, with fp16 A, B between them (a smaller error than one by one;
- * calls whose coefficients could leave fp16's range, and precond NONE, run one
- * by one).  f32 entry points store in fp32 and accumulate in fp32; matrices
- * with min(m, n) >= 64 are multiplied as two fp16 planes of 22 bits or more,
- * scaled row by row, the others (and the calls named above) in fp32.  Results
- * are deterministic: no float atomics.
+ * and one update, with fp16 A, B between them (about half the error of one by
+ * one; calls whose coefficients could leave fp16's range, and precond NONE, run
+ * one by one).  f32 entry points store in fp32 and accumulate in fp32; matrices
+ * with min(m, n) >= 64 are multiplied as two fp16 planes, scaled row by row, the
+ * others (and the calls named above) in fp32.  The planes hold an entry to 2^-22
+ * of itself, or to 2^-49 of its row's largest (between iterations, of sigma_max)
+ * where that is more: rows of any size keep their accuracy, entries and columns
+ * from about 2^-20 of the others.  In either form a row far below the others is
+ * worked on at a larger size under FROBENIUS and SCHATTEN4 and scaled back;
+ * behind AOL, which levels the rows, rows keep their accuracy from about 1e-14 of
+ * the others.  Results are deterministic (no float atomics) and do not depend on
+ * what else is in the call.
  *
  * Small matrices.  A bf16 call with iters >= 1 whose every matrix has
  * min(m, n) <= 128 and fits, zero padded to multiples of 32, in one compute

@@ -1056,7 +1056,7 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   const bool half = half_ok(iters, coeffs, precond, esz == 2 ? 32.0 : 16.0, &growth);
   const float raise = half && uniform ? raise_to(growth) : 0.f;
   // pairs (bf16), planes (fp32)
-  const bool fp16 = half && (!uniform || esz == 2 || raise > 0.f);
+  const bool fp16 = half && (!uniform || raise > 0.f);
   // What a call of these shapes needs in any form (they differ by iters, coefficients
   // and precond), on the smallest tile: reserved by every call, so that one call serves
   // the capture of any other of the same or smaller shapes.
@@ -1093,9 +1093,13 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
       pl[p].esz = esz;
       pl[p].st = st;
       pl[p].split = p == 0 && esz == 4;
-      pl[p].raise = pl[p].split ? raise : 0.f;
       if (p == 0) {
-        for (Item& it : part[p]) it.pair = esz == 2 && iters >= 2 && fp16 && pair_rule(it);
+        bool any16 = pl[p].split;
+        for (Item& it : part[p]) {
+          it.pair = esz == 2 && iters >= 2 && fp16 && pair_rule(it);
+          any16 = any16 || it.pair;
+        }
+        pl[p].raise = any16 ? raise : 0.f;
         pl[p].tcfg = layout_cfg(shapes_of(part[p]), esz, limit == UINT64_MAX ? limit : limit - std::min(limit, rest));
         for (Item& it : part[p]) {
           tmk::tiled_dims(it.k, it.N, uint32_t(tmk::cfg_tile(pl[p].tcfg)), &it.kp, &it.Np);

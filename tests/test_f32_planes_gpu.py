@@ -71,6 +71,19 @@ def test_few_small_rows_under_a_uniform_scale(k, N, precond, iters):
         assert np.linalg.norm(G[i] - R[i]) <= TOL * np.linalg.norm(R[i]), i
 
 
+@pytest.mark.parametrize("precond", ["aol", "frobenius"])
+def test_small_columns_keep_their_bits(precond):
+    """Columns at 2^-20 of the others: entries of about 2^-25 (400 columns), held to 2^-50 between
+    the iterations."""
+    log(f"case: small columns, {precond}")
+    X = make_input(96, 400, 0.8, 4, "f32")
+    X[:, ::7] *= 2.0 ** -20
+    R = O.orthogonalize(X, 4, None, precond)
+    G = one(X, 4, precond)
+    for j in range(0, 400, 7):
+        assert np.linalg.norm(G[:, j] - R[:, j]) <= TOL * np.linalg.norm(R[:, j]), j
+
+
 def test_large_coefficients_keep_the_fp32_instructions():
     log("case: linear steps of 1e3 in fp32")
     X = make_input(96, 400, 0.8, 5, "f32")

@@ -94,6 +94,23 @@ def test_zero_rows_and_zero_matrix():
     assert not from_device(one(0.0 * X, 4, "frobenius")).any()
 
 
+@pytest.mark.parametrize("precond", ["aol", "frobenius", "schatten4"])
+@pytest.mark.parametrize("tall", [False, True])
+def test_small_rows_keep_their_directions(precond, tall):
+    """Rows at 1e-9 of the others (their entries of A are below fp16's normal numbers): each comes
+    out within the tolerance of the whole matrix, by itself."""
+    log(f"case: rows at 1e-9, {precond} tall={tall}")
+    X = make_input(520, 2700, 0.8, 8, "bf16")
+    small = [0, 77, 300, 519]
+    X[small] *= 2.0 ** -30
+    G = from_device(one(X.T if tall else X, 4, precond))
+    G = G.T if tall else G
+    R = O.orthogonalize(X, 4, None, precond)
+    assert relF(G, R) <= BF16_TOL
+    for i in small:
+        assert np.linalg.norm(G[i] - R[i]) <= BF16_TOL * np.linalg.norm(R[i]), i
+
+
 def test_failed_allocation_leaves_a_mixed_group_untouched(monkeypatch):
     """Pairs beside matrices of the fused range, which need no workspace: still nothing is
     enqueued when the pairs' workspace cannot be had."""
