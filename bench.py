@@ -41,15 +41,14 @@ def alg_flops(k: int, N: int, iters: int) -> dict:
 
 
 def shares_updates(k: int, N: int, iters: int, dtype: str, precond: str) -> bool:
-    """Whether the library runs this matrix two iterations per update (its rule on sizes;
-    the default coefficients always allow it)."""
-    if dtype != "bf16" or precond == "none" or iters < 2:
+    """Whether the library runs this matrix two iterations per update (its rule on sizes and
+    iterations; the default coefficients allow it up to 7 iterations, after AOL always)."""
+    if dtype != "bf16" or precond == "none" or iters < 2 or k < 256:
         return False
-    if k >= 3072:
-        return 2 * N >= 3 * k
-    if k >= 1280:
-        return N >= 2 * k
-    return N >= 4 * k if k >= 512 else k >= 256 and N >= 9 * k
+    if precond != "aol" and iters > 7:
+        return False
+    line = max(2048, min(3 * k, 2560) if k < 1280 else k // 4)
+    return N - k >= (4096 if iters == 2 and k < 1536 else line)
 
 
 def run_flops(k: int, N: int, iters: int, dtype: str, precond: str) -> dict:

@@ -22,8 +22,8 @@
  * Arithmetic.  bf16 entry points store X, A and B in bfloat16 (round to
  * nearest even) and accumulate every product in fp32 on the matrix cores; the
  * AOL row sums are taken from the fp32 Gram accumulators.  Where the long side
- * is much the longer (max(m, n) at least 9 min(m, n) from min(m, n) = 256 on,
- * 4 from 512, 2 from 1280 and 1.5 from 3072 on), two iterations share one Gram
+ * is much the longer (max(m, n) - min(m, n) at least 2048 to 2560, min(m, n) at
+ * least 256; twice that for iters = 2), two iterations share one Gram
  * and one update, with fp16 A, B between them (about half the error of one by
  * one; calls whose coefficients could leave fp16's range, and precond NONE, run
  * one by one).  f32 entry points store in fp32 and accumulate in fp32; matrices

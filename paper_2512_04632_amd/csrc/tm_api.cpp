@@ -791,30 +791,59 @@ float raise_to(double growth) {
 // fewer operations still, but the Gram's rounding error then grows by a^2 for
 // every further iteration and passes the step-by-step form's on spectra with
 // many small singular values.
-// The line.  Measured, step by step and in pairs: 8 x 4096 x 14336 20.0 and 14.6 ms,
-// 2 x 2048 x 8192 1.23 and 0.97 ms, 64 conv matrices (N = 9 k) 534 and 427 us, one
-// 768 x 3072 matrix 125 and 122 us; but 1 x 1984 x 3072 421 and 514 us, 40 x 200 x 300
-// 118 and 130 us, 8 x 4096 x 4096 7.4 and 8.0 ms.  Square matrices do as many operations
-// either way, and a product of two different k x k matrices reads twice the bytes of
-// A A, which the smaller tiles (k below 3072 or so) feel.  Below k = 1280 the k x k
-// products of a few matrices are all latency (6 us each whatever they do), of which a
-// pair has three more in place of a Gram and an update, and beside other matrices of
-// the call that go step by step the two chains share only some of their launches
-// (45 matrices, three of them 1819 x 547: 390 us step by step, 424 with those in
-// pairs): there the long side has to be much the longer, as in the MLPs of transformers
-// (4 k) and in 3 x 3 convolutions (9 k).  The rule depends on the shape alone, so that a
+// The line.  Pairs save 3 (N - k) k^2 operations per two iterations and add three
+// dependent k x k products, each of a chain's 4 to 7 us below k = 1280 or so and
+// of two waves of tiles and more above.  Times in pairs over step by step, four
+// iterations, by N - k and matrices in the call (k = 64 to 8192 measured):
+//            1280           1536           1792           2048           3072
+//   k     1   4   24     1   4   24     1   4   24     1   4   24     1   4   24
+//   256  1.04 1.00 1.02 1.03 0.98 1.01 1.01 0.96 1.00 0.99 0.93 0.96 0.94 0.90 0.89
+//   512  1.03 1.01 0.88 1.03 1.00 0.87 0.98 0.95 0.83 0.98 0.93 0.85 0.94 0.90 0.67
+//   768  1.06 1.00 0.87 1.05 0.97 0.84 1.02 0.94 0.83 0.99 0.87 0.78 1.03 0.84 0.73
+//   1024 1.03 0.94 0.88 1.01 0.93 0.85 1.01 0.92 0.83 0.99 0.91 0.80 0.95 0.94 0.75
+//   1280 1.01 0.97 0.93 1.01 0.95 0.90 1.00 0.93 0.88 0.92 0.75 0.84 0.88 0.79 0.79
+//   2048 0.99 0.97      0.97 0.95      0.96 0.93      0.95 0.92      0.90 0.84
+//   3072 1.07 0.96      1.07 0.94      1.04 0.93      1.01 0.92      0.93
+//   8192 1.02           1.01           1.01           1.00           0.95
+// So a lone matrix breaks even where N - k is about 2048 whatever k (above 8192 k / 4
+// is assumed, as from 4096 to 8192), batches earlier.  Beside other matrices that go
+// step by step the two chains share only some of their launches, which is up to 50 us
+// more a call; three layers of four k x k, a k x N and an N x k matrix, pairs over step
+// by step by N - k:
+//   k      2048  2560  3072  4096        k      1024  1536  2048  2560  3072
+//   256    1.17  1.15  1.12  1.08        1024         1.05  1.05  1.00  0.95
+//   384    1.12  1.02  1.01  0.97        1152   1.08  1.03  1.00  0.97
+//   512    1.04  1.01        0.96        1280         1.07  1.04  1.01  0.95
+//   640    1.04  0.98  0.98              1408   1.02  0.98  0.95  0.93
+//   768    1.02  0.95  0.92  0.83        1536   1.01  0.99  0.99        0.94
+// (768 x 2688 1.02, 768 x 3072 0.96; 12 layers gain 3 to 10% at 2048 from k = 320 on; two
+// layers of 2048, 3072 and 4096 at 2048 1.00, 0.98 and 0.98.)  So around 768, where the
+// products of such a group fill a wave, the line is 3 k, up to 2560; from 1280 on 2048.
+// Below 683 it is the lone matrix's: 16 x 256 x 2304 beside the other 3 x 3 convolutions of
+// a ResNet, which run fused or in pairs, 464 and 416 us (but 12 x 256 x 256 with
+// 2 x 256 x 2304 93 and 115); below 256 a call is too short to make up for a loss
+// (8 x 128 x 512 with 2 x 192 x 2240 88 and 108).  Three iterations (one pair and one step) break
+// even where four do (768: 1.00, 1024: 1.00, 2048: 0.98 at 2048); two alone twice as far
+// (768 x 3840 1.20, 512 x 4608 1.00, 1024 x 5120 0.94) but from k = 1536 on (2048 x 4096 1.01
+// and, 8 of them, 0.94).  The rule depends on the shape and iters alone, so that a
 // matrix comes out the same from a single, a batched and a grouped call.
-bool pair_rule(const Item& it) {
-  const uint64_t k = it.k, N = it.N;
-  if (k >= 3072) return 2 * N >= 3 * k;
-  if (k >= 1280) return N >= 2 * k;
-  return k >= 512 ? N >= 4 * k : (k >= 256 && N >= 9 * k);
+bool pair_rule(const Item& it, int iters) {
+  const uint64_t k = it.k, d = uint64_t(it.N) - it.k;
+  if (k < 256 || iters < 2) return false;
+  const uint64_t line = std::max<uint64_t>(2048, k < 1280 ? std::min<uint64_t>(3 * k, 2560) : k / 4);
+  return d >= (iters == 2 && k < 1536 ? 4096 : line);
 }
 
-// fp32 matrices on fp16 planes: 4096 x 4096 12.65 -> 4.9 ms, 256 x 256 162 -> 105 us,
-// with a third of the error against 64 bits.  Short sides below 64 would be mostly padding
-// of the 64-wide tiles (a batch of many tiny matrices would need a workspace
-// several times its size).
+// fp32 matrices on fp16 planes.  Times on the fp32 products and on planes: 4096 x 4096
+// 12.65 and 3.4 ms, 256 x 256 162 and 105 us, 600 of 64 x 64 1.20 and 0.15 ms, of
+// 65 x 65 (128 x 128 as padded) 1.67 and 0.38, of 129 x 129 3.1 and 0.91, of 193 x 1000 10.7
+// and 4.5; the closest of 400 calls from k = 64 to 385 64 x 96 x 96, 108.9 and 110.9 us.  Errors
+// against 64 bits, planes over fp32: 0.31 to 0.86, median 0.51 (k = 64 to 1024, N = 1 to
+// 9 k, every scale, 3 to 5 iterations): fewer roundings in the sums outweigh the planes'
+// 22 to 23 bits.  The line is the smallest tile.  Planes are faster below it too (600 of
+// 34 x 34 1.12 and 0.15 ms, one of 63 x 63 80 and 74 us), but there the padding of k
+// alone is a workspace of up to (64 / k)^2 times the size, and short sums are not where
+// planes gain accuracy (64 x 64: 0.62).
 bool split_rule(const Item& it) { return it.k >= 64; }
 
 // The k x k products and update of iterations [it, it + n) of one class (1:
@@ -1065,9 +1094,9 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
   // those there, in one launch: step by step on tiles they would add about eight
   // launches to the pairs' chain.  (Bit for bit the same results.)
   std::vector<Item> small;
-  if (esz == 2 && iters >= 2 && fp16 && std::getenv("TM_DISABLE_FUSED") == nullptr) {
+  if (esz == 2 && fp16 && std::getenv("TM_DISABLE_FUSED") == nullptr) {
     std::vector<Item> pairs;
-    for (const Item& it : items) (pair_rule(it) ? pairs : small).push_back(it);
+    for (const Item& it : items) (pair_rule(it, iters) ? pairs : small).push_back(it);
     if (!pairs.empty() && std::all_of(small.begin(), small.end(), small_eligible)) items = pairs;
     else small.clear();
   }
@@ -1096,7 +1125,7 @@ tm_status run_locked(std::vector<Item>& items, int esz, int iters, const float* 
       if (p == 0) {
         bool any16 = pl[p].split;
         for (Item& it : part[p]) {
-          it.pair = esz == 2 && iters >= 2 && fp16 && pair_rule(it);
+          it.pair = esz == 2 && fp16 && pair_rule(it, iters);
           any16 = any16 || it.pair;
         }
         pl[p].raise = any16 ? raise : 0.f;
@@ -1434,10 +1463,10 @@ uint64_t tm_workspace_bytes(const int64_t* m, const int64_t* n, int64_t count, i
     return shapes.empty() ? 0 : laid_bytes(shapes, layout_cfg(shapes, dtype_bytes), dtype_bytes);
   };
   uint64_t most = bytes(tiled);
-  if (dtype_bytes == 2) {
+  for (int iters = 2; dtype_bytes == 2 && iters <= 3; ++iters) {   // pair_rule's two lines
     std::vector<Item> pairs;
     for (Item& it : tiled) {
-      it.pair = pair_rule(it);
+      it.pair = pair_rule(it, iters);
       if (it.pair) pairs.push_back(it);
     }
     most = std::max(most, std::max(bytes(tiled), bytes(pairs)));

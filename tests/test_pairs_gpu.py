@@ -1,7 +1,10 @@
-"""Two iterations per update (bf16, N at least 9 k from k = 256 on, 4 k from 512 on, 2 k
-from 1280 on and 1.5 k from 3072 on): the k x k products of tm_fast.hip against the fp64 oracle at the edges of the tiles
-and of the rule, for even and odd iteration counts, and equal bits from single, batched and
-grouped calls that run different tiles."""
+"""Two iterations per update (bf16, k at least 256 and N - k at least 2048, up to 2560 for k
+from 683 to 1279): the k x k products of tm_fast.hip against the fp64 oracle at the edges of the
+tiles and of the rule, for even and odd iteration counts, and equal bits from single, batched
+and grouped calls that run different tiles."""
+import importlib.util
+import os
+
 import numpy as np
 import pytest
 
@@ -15,16 +18,22 @@ torch = pytest.importorskip("torch")
 from paper_2512_04632_amd import _lib as tm  # noqa: E402
 
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
 def one(X, iters, precond, coeffs=None):
     t = to_device(X, "bf16")
     tm.orthogonalize(t, iters, coeffs, precond)
     return t
 
 
-# (k, N): the edges of the rule (256 x 2304, 512 x 2048 and 1280 x 2560 are in, 257 x 2304,
-# 513 x 2048 and 1281 x 2560 out), tile remainders on either side, ragged N
+# (k, N): the edges of the rule (256 x 2304, 640 x 2688, 768 x 3072 and 1280 x 3328 are in,
+# 256 x 2303, 255 x 2400, 640 x 2687, 768 x 3071, 1279 x 3328 and 1280 x 3327 out), tile
+# remainders on either side, ragged N
 SHAPES = [(256, 2304), (257, 2304), (300, 2701), (512, 2048), (513, 2048), (513, 2100),
-          (575, 2333), (577, 2900), (640, 3000), (1280, 2560), (1281, 2560)]
+          (575, 2333), (577, 2900), (640, 3000), (1280, 2560), (1281, 2560),
+          (255, 2400), (256, 2303), (300, 2348), (640, 2687), (640, 2688), (768, 3071), (768, 3072),
+          (1280, 3328)]
 
 
 @pytest.mark.parametrize("k,N", SHAPES)
@@ -45,47 +54,75 @@ def test_pairs_match_oracle(k, N, precond, iters, coeffs):
             assert abs(eo_ratio(G, R) - 1) <= EO_RATIO_TOL
 
 
+@pytest.mark.parametrize("k,N,iters,precond", [
+    (k, N, t, p) for k, N in ((255, 2400), (256, 2303), (256, 2304), (640, 2687), (640, 2688), (768, 3071),
+                              (768, 3072), (1000, 3560), (1279, 3838), (1279, 3839), (1280, 3327), (1280, 3328),
+                              (1535, 4000), (1536, 3584), (1000, 5096))
+    for t, p in ((2, "aol"), (3, "aol"), (4, "aol"), (5, "frobenius"), (8, "frobenius"), (4, "none"))])
+def test_benchmark_counts_the_updates_that_run(k, N, iters, precond):
+    """bench.py holds its own copy of the rule: the updates launched by one matrix (at most one
+    full wave of tiles, so one launch each) are those that it counts."""
+    log(f"case: updates of {k}x{N} t={iters} {precond}")
+    spec = importlib.util.spec_from_file_location("tm_bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    t = (torch.randn((k, N), device="cuda") / (k ** 0.5 + N ** 0.5)).bfloat16()
+    tm.timing_reset()
+    tm.timing_enable(True)
+    try:
+        tm.orthogonalize(t, iters, None, precond)
+        torch.cuda.synchronize()
+    finally:
+        tm.timing_enable(False)
+    ran = tm.timing_read("update")[1]
+    tm.timing_reset()
+    assert ran == bench.run_flops(k, N, iters, "bf16", precond)["updates"]
+
+
 def test_mixed_group_equals_single_calls_bitwise():
     """Pairs, step-by-step and fused-range matrices in one call: every launch covers other
     matrices, with other tiles, than the single calls'."""
     log("case: mixed group vs single calls, bitwise")
     shapes = [(768, 3072), (515, 515), (64, 576), (129, 1153), (1001, 777), (300, 375), (2048, 640),
-              (1300, 2700),
+              (1300, 2700), (2900, 640), (1300, 3400),
               (768, 3072), (40, 41)]
     Xs = [make_input(m, n, 0.8, i, "bf16") for i, (m, n) in enumerate(shapes)]
     for precond, iters, part in (("aol", 4, Xs), ("frobenius", 5, Xs), ("schatten4", 3, Xs),
-                                 ("aol", 4, [Xs[0], Xs[2], Xs[9]])):   # pairs and fused only
+                                 ("aol", 4, [Xs[0], Xs[2], Xs[11]])):   # pairs and fused only
         ts = [to_device(X, "bf16") for X in part]
         tm.orthogonalize_grouped(ts, iters, None, precond)
         for i, X in enumerate(part):
             assert torch.equal(ts[i], one(X, iters, precond)), (precond, X.shape)
 
 
+@pytest.mark.parametrize("N", [2100, 2700])   # step by step, in pairs
 @pytest.mark.parametrize("scale", [30.0, 1e3])
-def test_large_coefficients_stay_finite(scale):
+def test_large_coefficients_stay_finite(scale, N):
     """Coefficients whose k x k matrices could leave fp16's range take the bf16
     step-by-step form: linear steps (scale, 0, 0) multiply by scale each."""
     log(f"case: linear steps of {scale}")
-    X = make_input(520, 2100, 0.8, 5, "bf16")
+    X = make_input(520, N, 0.8, 5, "bf16")
     co = [(scale, 0.0, 0.0)] * 4
     G = from_device(one(X, 4, "aol", co))
     R = O.orthogonalize(X, 4, co, "aol")
     assert np.isfinite(G).all() and relF(G, R) <= BF16_TOL
 
 
+@pytest.mark.parametrize("N", [2048, 2600])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
-def test_non_finite_input_stays_visible(bad):
+def test_non_finite_input_stays_visible(bad, N):
     """One NaN or infinity reaches every output, as in the step-by-step form (its row sum
     scales every row)."""
     log(f"case: {bad} in the input")
-    X = make_input(512, 2048, 0.8, 6, "bf16")
+    X = make_input(512, N, 0.8, 6, "bf16")
     X[5, 7] = bad
     assert np.isnan(from_device(one(X, 4, "aol"))).all()
 
 
-def test_zero_rows_and_zero_matrix():
+@pytest.mark.parametrize("N", [2200, 2700])
+def test_zero_rows_and_zero_matrix(N):
     log("case: zero rows, zero matrix")
-    X = make_input(530, 2200, 0.8, 7, "bf16")
+    X = make_input(530, N, 0.8, 7, "bf16")
     X[3] = 0.0
     X[529] = 0.0
     G = from_device(one(X, 4, "aol"))
