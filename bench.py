@@ -20,7 +20,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 matrix-core peak (published)
+PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 and fp16 matrix-core peak (published)
 PEAK_F32_TFLOPS = 157.3
 HBM_GBPS = 8000.0
 
@@ -51,17 +51,28 @@ def shares_updates(k: int, N: int, iters: int, dtype: str, precond: str) -> bool
     return N - k >= (4096 if iters == 2 and k < 1536 else line)
 
 
+def on_planes(k: int, iters: int, dtype: str, precond: str) -> bool:
+    """Whether the library multiplies this fp32 matrix as two fp16 planes (as shares_updates)."""
+    return (dtype == "f32" and k >= 64 and iters > 0 and precond != "none"
+            and (precond == "aol" or iters <= 7))
+
+
 def run_flops(k: int, N: int, iters: int, dtype: str, precond: str) -> dict:
-    """Operations that the library carries out per matrix: of two iterations per update one
-    Gram, five k x k products (upper triangles) and one update; else as alg_flops."""
+    """Operations that the library carries out per matrix, and the dense peak of the instructions
+    that do them: of two iterations per update one Gram, five k x k products (upper triangles)
+    and one update; of fp32 on fp16 planes three fp16 products for one; else as alg_flops."""
     fl = alg_flops(k, N, iters)
     upd = fl["update_per_iter"]
+    if on_planes(k, iters, dtype, precond):
+        return {"total": 3 * fl["total"], "update": 3 * upd * iters, "updates": iters,
+                "peak": PEAK_BF16_TFLOPS}
     if not shares_updates(k, N, iters, dtype, precond):
-        return {"total": fl["total"], "update": upd * iters, "updates": iters}
+        return {"total": fl["total"], "update": upd * iters, "updates": iters,
+                "peak": PEAK_BF16_TFLOPS if dtype == "bf16" else PEAK_F32_TFLOPS}
     one, two = iters % 2, iters // 2
     gram, prod = k * (k + 1) * N, k * k * (k + 1)
     return {"total": two * (gram + 5 * prod + upd) + one * (fl["total"] // iters),
-            "update": upd * (two + one), "updates": two + one}
+            "update": upd * (two + one), "updates": two + one, "peak": PEAK_BF16_TFLOPS}
 
 
 def main(argv=None) -> int:
@@ -204,12 +215,15 @@ def main(argv=None) -> int:
     step_flops = 0
     done_flops = 0
     upd_flops = 0
+    peak_us = upd_peak_us = 0.0      # time of the operations carried out at their peaks
     for count, m, n, _ in entries:
         fl = alg_flops(min(m, n), max(m, n), args.iters)
         step_flops += fl["total"] * count
         rf = run_flops(min(m, n), max(m, n), args.iters, dtype, args.precond)
         done_flops += rf["total"] * count
         upd_flops += rf["update"] * count
+        peak_us += rf["total"] * count / rf["peak"] / 1e6
+        upd_peak_us += rf["update"] * count / rf["peak"] / 1e6
     done_tflops = done_flops / (ms_per_step * 1e-3) / 1e12
     tflops = step_flops / (ms_per_step * 1e-3) / 1e12
     upd_ms, upd_n = phases["update"]
@@ -220,7 +234,8 @@ def main(argv=None) -> int:
     upd_flops_per_launch = (upd_flops_total // upd_n if upd_n and upd_flops_total % upd_n == 0
                             else (upd_flops_total / upd_n if upd_n else 0))
     upd_tflops = upd_flops_total / (upd_ms * 1e-3) / 1e12 if upd_n else None
-    peak = PEAK_BF16_TFLOPS if dtype == "bf16" else PEAK_F32_TFLOPS
+    # peak of the updates' instructions (of several kinds, what they reach together at theirs)
+    peak = round(upd_flops / upd_peak_us / 1e6, 2) if upd_peak_us else PEAK_BF16_TFLOPS
 
     config = {"workload": args.workload, "matrices": n_mat,
               "shapes": [[c, m, n] for c, m, n, _ in entries],
@@ -244,10 +259,11 @@ def main(argv=None) -> int:
                  if args.inputs == "powerlaw" else "synthetic (seeded i.i.d. N(0,1))"),
         "config": config,
         # operations of the iteration as printed, and those carried out (matrices whose
-        # long side is much the longer take two iterations per update, which is fewer)
+        # long side is much the longer take two iterations per update, which is fewer; an fp32
+        # product on fp16 planes is three, against the fp16 peak)
         "tflops_algorithmic": round(tflops, 2),
         "tflops_done": round(done_tflops, 2),
-        "pct_peak": round(100 * done_tflops / peak, 2),
+        "pct_peak": round(100 * peak_us / (ms_per_step * 1e3), 2),
         "phase_ms_per_step": {p: round(v[0] / args.steps, 4) for p, v in phases.items()},
         "roofline": {"bound": "mfma", "kernel": "k_update_fast",
                      "achieved": round(upd_tflops, 2) if upd_n else None, "peak": peak,
@@ -417,16 +433,16 @@ def _config_records(args, dev, progress):
                 del os.environ["TM_DISABLE_FUSED"]
         n_mat = sum(c for c, _, _, _ in entries)
         flops = sum(alg_flops(min(m, n), max(m, n), iters)["total"] * c for c, m, n, _ in entries)
-        done = sum(run_flops(min(m, n), max(m, n), iters, spec["dtype"], precond)["total"] * c
-                   for c, m, n, _ in entries)
-        peak = PEAK_BF16_TFLOPS if dtype == "bf16" else PEAK_F32_TFLOPS
+        ran = [(run_flops(min(m, n), max(m, n), iters, spec["dtype"], precond), c) for c, m, n, _ in entries]
+        done = sum(rf["total"] * c for rf, c in ran)
+        peak_us = sum(rf["total"] * c / rf["peak"] / 1e6 for rf, c in ran)
         rec = {"config": label, "workload": wl, "call": "grouped" if grouped else "batched",
                "shapes": [[c, m, n] for c, m, n, _ in entries], "dtype": dtype, "iters": iters,
                "precond": precond, "steps": steps, "ms_per_step": round(ms, 4),
                "matrices_per_s": round(n_mat / (ms * 1e-3), 2),
                "tflops_algorithmic": round(flops / (ms * 1e-3) / 1e12, 2),
                "tflops_done": round(done / (ms * 1e-3) / 1e12, 2),
-               "pct_peak": round(100 * done / (ms * 1e-3) / 1e12 / peak, 2),
+               "pct_peak": round(100 * peak_us / (ms * 1e3), 2),
                "kernels": "fused" if fused else "tiled"}
         if tiled_ms is not None:
             rec["tiled_ms_per_step"] = round(tiled_ms, 4)
