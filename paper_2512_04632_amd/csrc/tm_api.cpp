@@ -571,17 +571,25 @@ tm_status launch(const Plan& pl, int kind, int cfg, int src, int dst, float a, f
     // GPT-2 and 64 conv matrices within 0.4%).  Slices also stand in for the
     // sub-tiles of a nearly empty last wave (below), where the shortest tiles are
     // last: 20 x 1024 x 1024 with 8 x 1024 x 1800 902 us, with sub-tiles 952.
+    // Not for entries of one matrix, which eight L2s then share, nor for many entries,
+    // which every block walks through: groups of single matrices, slices and chunks, 40
+    // shapes 480 and 361 us, 24 of them 294 and 244, 12 675 and 640, 6 404 and 388, 3 88
+    // and 85; of three each, 40 shapes 1055 and 938, 24 680 and 632, 16 1342 and 1517 (360
+    // and 337 with lengths closer together), 8 819 and 879.
     const bool mc = kind == tmk::kKindGram || kind == tmk::kKindPoly || kind == tmk::kKindUpdate;
     bool by_slice = false;
     if ((pl.esz == 2 || pl.split) && mc) {
       uint32_t kmin = UINT32_MAX, kmax = 0;
+      uint64_t ents = 0, mats = 0;
       for (int e = 0; e < P.nent; ++e) {
         if (P.e[e].tiles_per == 0u) continue;
         const uint32_t K = kind == tmk::kKindGram ? P.e[e].Np : P.e[e].kp;
         kmin = std::min(kmin, K);
         kmax = std::max(kmax, K);
+        ++ents;
+        mats += P.e[e].count;
       }
-      by_slice = kmin < kmax;
+      by_slice = kmin < kmax && ents <= 16 && 2 * mats >= 3 * ents;
       if (by_slice) P.flags |= tmk::kBySlice;
     }
     // bf16 matrix-core phases on 256 x 256 tiles whose last wave would be at

@@ -170,6 +170,7 @@ def test_failed_allocation_leaves_a_mixed_group_untouched(monkeypatch):
     [(200, 260)] * 9 + [(1000, 600)] + [(130, 2000)] * 3,        # the longest products last
     [(300, 500)] * 20 + [(500, 1999)] * 5 + [(1000, 1200)] * 2,  # more than two waves of tiles
     [(300, 400), (250, 900), (900, 1000)] + [(2048, 2048)] * 4,  # larger tiles than the single calls'
+    [(100 + 17 * i, 160 + 31 * i) for i in range(20)],           # too many entries for shares
 ])
 @pytest.mark.parametrize("precond", ["aol", "schatten4"])   # two reductions of the first Gram
 def test_mixed_lengths_equal_single_calls(dtype, shapes, precond):
