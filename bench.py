@@ -47,7 +47,7 @@ def shares_updates(k: int, N: int, iters: int, dtype: str, precond: str) -> bool
         return False
     if precond != "aol" and iters > 7:
         return False
-    line = max(2048, min(3 * k, 2560) if k < 1280 else k // 4)
+    line = max(2048, min(3 * k, 2560)) if k < 1280 else k if k < 2048 else max(2048, k // 4)
     return N - k >= (4096 if iters == 2 and k < 1536 else line)
 
 

@@ -22,8 +22,8 @@
  * Arithmetic.  bf16 entry points store X, A and B in bfloat16 (round to
  * nearest even) and accumulate every product in fp32 on the matrix cores; the
  * AOL row sums are taken from the fp32 Gram accumulators.  Where the long side
- * is much the longer (max(m, n) - min(m, n) at least 2048 to 2560, min(m, n) at
- * least 256; twice that for iters = 2), two iterations share one Gram
+ * is much the longer (max(m, n) - min(m, n) at least 1280 to 2560 by min(m, n),
+ * which is at least 256; 4096 for iters = 2 below 1536), two iterations share one Gram
  * and one update, with fp16 A, B between them (about half the error of one by
  * one; calls whose coefficients could leave fp16's range, and precond NONE, run
  * one by one).  f32 entry points store in fp32 and accumulate in fp32; matrices

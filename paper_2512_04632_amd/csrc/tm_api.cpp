@@ -826,7 +826,9 @@ float raise_to(double growth) {
 //   768    1.02  0.95  0.92  0.83        1536   1.01  0.99  0.99        0.94
 // (768 x 2688 1.02, 768 x 3072 0.96; 12 layers gain 3 to 10% at 2048 from k = 320 on; two
 // layers of 2048, 3072 and 4096 at 2048 1.00, 0.98 and 0.98.)  So around 768, where the
-// products of such a group fill a wave, the line is 3 k, up to 2560; from 1280 on 2048.
+// products of such a group fill a wave, the line is 3 k, up to 2560.  From 1280 on, where
+// a few matrices fill the chip, it is k, up to 2048: 2 x 1555 x 3182 461 and 413 us,
+// 9 x 1396 x 3144 (3 iterations) 846 and 784, against 2 to 5% in such mixed groups.
 // Below 683 it is the lone matrix's: 16 x 256 x 2304 beside the other 3 x 3 convolutions of
 // a ResNet, which run fused or in pairs, 464 and 416 us (but 12 x 256 x 256 with
 // 2 x 256 x 2304 93 and 115); below 256 a call is too short to make up for a loss
@@ -838,7 +840,8 @@ float raise_to(double growth) {
 bool pair_rule(const Item& it, int iters) {
   const uint64_t k = it.k, d = uint64_t(it.N) - it.k;
   if (k < 256 || iters < 2) return false;
-  const uint64_t line = std::max<uint64_t>(2048, k < 1280 ? std::min<uint64_t>(3 * k, 2560) : k / 4);
+  const uint64_t line = k < 1280 ? std::max<uint64_t>(2048, std::min<uint64_t>(3 * k, 2560))
+                                 : (k < 2048 ? k : std::max<uint64_t>(2048, k / 4));
   return d >= (iters == 2 && k < 1536 ? 4096 : line);
 }
 

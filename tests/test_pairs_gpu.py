@@ -1,5 +1,5 @@
 """Two iterations per update (bf16, k at least 256 and N - k at least 2048, up to 2560 for k
-from 683 to 1279): the k x k products of tm_fast.hip against the fp64 oracle at the edges of the
+from 683 to 1279 and k from 1280 to 2047): the k x k products of tm_fast.hip against the fp64 oracle at the edges of the
 tiles and of the rule, for even and odd iteration counts, and equal bits from single, batched
 and grouped calls that run different tiles."""
 import importlib.util
@@ -27,13 +27,13 @@ def one(X, iters, precond, coeffs=None):
     return t
 
 
-# (k, N): the edges of the rule (256 x 2304, 640 x 2688, 768 x 3072 and 1280 x 3328 are in,
-# 256 x 2303, 255 x 2400, 640 x 2687, 768 x 3071, 1279 x 3328 and 1280 x 3327 out), tile
+# (k, N): the edges of the rule (256 x 2304, 640 x 2688, 768 x 3072 and 1280 x 2560 are in,
+# 256 x 2303, 255 x 2400, 640 x 2687, 768 x 3071, 1279 x 2560 and 1281 x 2560 out), tile
 # remainders on either side, ragged N
 SHAPES = [(256, 2304), (257, 2304), (300, 2701), (512, 2048), (513, 2048), (513, 2100),
           (575, 2333), (577, 2900), (640, 3000), (1280, 2560), (1281, 2560),
           (255, 2400), (256, 2303), (300, 2348), (640, 2687), (640, 2688), (768, 3071), (768, 3072),
-          (1280, 3328)]
+          (1279, 2560)]
 
 
 @pytest.mark.parametrize("k,N", SHAPES)
@@ -56,8 +56,8 @@ def test_pairs_match_oracle(k, N, precond, iters, coeffs):
 
 @pytest.mark.parametrize("k,N,iters,precond", [
     (k, N, t, p) for k, N in ((255, 2400), (256, 2303), (256, 2304), (640, 2687), (640, 2688), (768, 3071),
-                              (768, 3072), (1000, 3560), (1279, 3838), (1279, 3839), (1280, 3327), (1280, 3328),
-                              (1535, 4000), (1536, 3584), (1000, 5096))
+                              (768, 3072), (1000, 3560), (1279, 3838), (1279, 3839), (1280, 2559), (1280, 2560),
+                              (1535, 4000), (1536, 3071), (1536, 3072), (1000, 5096))
     for t, p in ((2, "aol"), (3, "aol"), (4, "aol"), (5, "frobenius"), (8, "frobenius"), (4, "none"))])
 def test_benchmark_counts_the_updates_that_run(k, N, iters, precond):
     """bench.py holds its own copy of the rule: the updates launched by one matrix (at most one
