@@ -1023,8 +1023,10 @@ __device__ inline void store_rows_user(const char* st, uint16_t* dst, int k, int
     if (vec && l + 8 <= N) {
       *reinterpret_cast<uint4*>(p) = v;
     } else {
-      const uint16_t* e = reinterpret_cast<const uint16_t*>(&v);
-      for (int u = 0; u < 8 && l + u < N; ++u) p[u] = e[u];
+      const uint32_t e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int u = 0; u < 8; ++u)   // (with the count as the loop's end, e would sit in scratch memory)
+        if (l + u < N) p[u] = uint16_t(e[u >> 1] >> (16 * (u & 1)));
     }
   }
 }
@@ -1048,7 +1050,9 @@ __device__ inline void store_cols_user(const char* st, uint16_t* dst, int k, int
     if (vec && i + 8 <= k) {
       *reinterpret_cast<uint4*>(p) = *reinterpret_cast<const uint4*>(v);
     } else {
-      for (int u = 0; u < 8 && i + u < k; ++u) p[u] = v[u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (i + u < k) p[u] = v[u];
     }
   }
 }
