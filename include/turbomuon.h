@@ -129,7 +129,7 @@ typedef int tm_status;
 tm_status tm_orthogonalize(void* X, int64_t m, int64_t n, int64_t batch, int iters,
                            const float* coeffs, int precond, void* stream);
 
-/* Same contract with fp32 storage and fp32 matrix-core arithmetic. */
+/* Same contract with fp32 storage (products as stated under Arithmetic). */
 tm_status tm_orthogonalize_f32(float* X, int64_t m, int64_t n, int64_t batch, int iters,
                                const float* coeffs, int precond, void* stream);
 
@@ -241,8 +241,9 @@ tm_status tm_release_workspaces(void);
 #define TM_PHASE_UPDATE        5  /* X <- a X + B X */
 #define TM_PHASE_APPLY_SCALE   6  /* iters = 0: X1 = diag(s) X0 */
 #define TM_PHASE_COPY_OUT      7  /* iters = 1: result copied into the caller's buffer */
-#define TM_PHASE_LOAD_IN       8  /* bf16: X (or X^T) copied into the zero-padded workspace */
-#define TM_PHASE_SCALE_A       9  /* bf16: A1 = diag(s) A0 diag(s) (X1 is never stored: the first
+#define TM_PHASE_LOAD_IN       8  /* X (or X^T) copied into the zero-padded workspace; fp32: row maxima,
+                                    then the fp16 planes */
+#define TM_PHASE_SCALE_A       9  /* tiled kernels: A1 = diag(s) A0 diag(s) (X1 is never stored: the first
                                     polynomial keeps B~ diag(s) and the update reads X0) */
 #define TM_PHASE_OPT_MOMENTUM 10  /* optimizer step: momentum and the bf16 matrix to orthogonalize */
 #define TM_PHASE_OPT_APPLY    11  /* optimizer step: parameter update */

@@ -250,7 +250,7 @@ double launch_us(int kind, int cfg, const std::vector<Item>& items, int segments
 }
 
 // The tile of a launch: cfg first .. last from the largest tile down, a
-// smaller one where the model puts it 10% ahead (within that, the larger tile
+// smaller one where the model puts it 5% ahead (within that, the larger tile
 // measured better: the 64 conv matrices' Gram on 240 tiles of 128 against 800
 // of 64 by 9%).
 int choose_cfg(int kind, int first, int last, const std::vector<Item>& items, int segments) {

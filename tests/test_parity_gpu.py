@@ -299,12 +299,12 @@ def test_grouped_gpt2_small_matches_single_calls_bitwise():
     torch.cuda.synchronize()
 
 
-def test_grouped_mixed_k_dealt_by_matrix_matches_single_calls():
+def test_grouped_mixed_k_by_slices_matches_single_calls():
     """A grouped launch whose Gram tiles differ in K gives every XCD an eighth of
     each entry: 24 matrices of 256 x 2048 and 30 of 256 x 512 (540 Gram tiles of
     64).  Every matrix equals its own single call bit for bit, and a sample of each
     shape the oracle."""
-    log("case: grouped 24 x 256x2048 + 30 x 256x512, by-matrix dealing")
+    log("case: grouped 24 x 256x2048 + 30 x 256x512, an eighth of each entry per XCD")
     shapes = [(256, 2048)] * 24 + [(256, 512)] * 30
     Xs = [make_input(m, n, 0.8, 500 + i, "bf16") for i, (m, n) in enumerate(shapes)]
     ts = [to_device(X, "bf16") for X in Xs]
