@@ -30,8 +30,8 @@
  * with min(m, n) >= 64 are multiplied as two fp16 planes, scaled row by row, the
  * others (and the calls named above) in fp32.  The planes hold an entry to 2^-22
  * of itself, or to 2^-49 of its row's largest (between iterations, of sigma_max)
- * where that is more: rows of any size keep their accuracy, entries and columns
- * from about 2^-20 of the others.  In either form a row far below the others is
+ * where that is more: rows of any size whose squares fp32 holds (1e-18 and more)
+ * keep their accuracy, entries and columns from about 2^-20 of the others.  In either form a row far below the others is
  * worked on at a larger size under FROBENIUS and SCHATTEN4 and scaled back;
  * behind AOL, which levels the rows, rows keep their accuracy from about 1e-14 of
  * the others.  Results are deterministic (no float atomics) and do not depend on

@@ -782,7 +782,8 @@ bool half_ok(int iters, const float* coeffs, int precond, double top_b, double* 
 // (pairs), as the others are.  2^-14 is too large (1e-5), 2^-22 begins to show the
 // formats' resolution (2e-6): from a growth of 2^14 on (8 iterations of the default
 // coefficients) neither fits, and uniform scales keep the fp32 products and the
-// step-by-step form.  0: no raise there.
+// step-by-step form.  0: no raise there.  (A row's size is that of its A0_ii: one whose
+// squares underflow, below 1e-19 itself, stays as it is.)
 float raise_to(double growth) {
   const int e = -8 - int(std::ceil(std::log2(growth)));
   return e < -22 ? 0.f : std::ldexp(1.f, std::min(e, -18));
